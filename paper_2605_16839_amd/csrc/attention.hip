@@ -640,41 +640,66 @@ __global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_ker
     l_run[c] = 0.f;
   }
 
-  int e_end = e1;
-  if (DENSE) {
-    // a split may start past the tile's last visible block: then it is empty
-    e_end = e1 < j_last + 1 ? e1 : j_last + 1;
-    e_end = e_end > e0 ? e_end : e0;
-  } else {
-    while (e_end > e0 && a.kv_indices[tbase + e_end - 1] > j_last) --e_end;
-  }
-  const int n = e_end - e0;
-  int n_main = n;
-  while (n_main > 0 &&
-         kPage * (DENSE ? e0 + n_main - 1 : a.kv_indices[tbase + e0 + n_main - 1]) + kPage - 1 >
-             mask_from)
-    --n_main;
-  // pages run by the software-pipelined loop: an even number of unmasked ones
-  const int n_pipe = n_main & ~1;
-
+  // The piece's entries: the first two windows of 64 block ids and their page
+  // ids, and the last window, whose trailing entries past the tile's last
+  // visible block are dropped and whose causally masked ones run apart.  Every
+  // load is issued before any is needed, so the prologue waits for two memory
+  // latencies (block ids, page ids) instead of one per trailing entry; the
+  // windows are read up to e1, so they do not wait for the trimmed count.
+  const int n_all = e1 - e0;
   SPage<NCT> SA, SB;
   PFrag<NCT> PA, PB;
   int base = 0, blk_cur = 0, pg_cur = 0, blk_nxt = 0, pg_nxt = 0;
   auto fetch = [&](int b0, int& blk, int& pg) {
     int idx = b0 + lane;
-    idx = idx < n ? idx : n - 1;
+    idx = idx < n_all ? idx : n_all - 1;
     idx = idx < 0 ? 0 : idx;
-    blk = (n > 0) ? (DENSE ? e0 + idx : a.kv_indices[tbase + e0 + idx]) : 0;
+    blk = (n_all > 0) ? (DENSE ? e0 + idx : a.kv_indices[tbase + e0 + idx]) : 0;
     if (!DENSE && a.table_mode == kTablesPacked) {
       // packed pools hold the selected pages in table order (copy arm)
       const long long pp = (long long)tbase + e0 + idx;
-      pg = (n > 0) ? (int)(pp < a.packed_pages ? pp : a.packed_pages - 1) : 0;
+      pg = (n_all > 0) ? (int)(pp < a.packed_pages ? pp : a.packed_pages - 1) : 0;
     } else {
-      pg = (n > 0) ? ptab[blk] : 0;
+      pg = (n_all > 0) ? ptab[blk] : 0;
     }
   };
-  fetch(0, blk_cur, pg_cur);
-  fetch(64, blk_nxt, pg_nxt);
+  int n, n_main;
+  if (DENSE) {
+    // a split may start past the tile's last visible block: then it is empty
+    n = (e1 < j_last + 1 ? e1 : j_last + 1) - e0;
+    n = n > 0 ? n : 0;
+    // unmasked pages: 64 j + 63 <= mask_from
+    n_main = (mask_from + 1) / kPage - e0;
+    n_main = n_main < 0 ? 0 : (n_main > n ? n : n_main);
+    fetch(0, blk_cur, pg_cur);
+    fetch(64, blk_nxt, pg_nxt);
+  } else {
+    int w1 = n_all, past_end = 0, masked = 0;
+    auto last_window = [&](int end) -> int {   // lane l: entry end - 64 + l, -1 before the piece
+      const int idx = end - kWave + lane;
+      return idx >= 0 ? a.kv_indices[tbase + e0 + idx] : -1;
+    };
+    int blk_last = last_window(w1);
+    fetch(0, blk_cur, pg_cur);
+    fetch(64, blk_nxt, pg_nxt);
+    for (;;) {
+      // tables are ascending: the entries past j_last come last, the masked
+      // ones before them
+      const bool gone = blk_last > j_last;
+      const bool mask = !gone && kPage * blk_last + kPage - 1 > mask_from;
+      const int n_gone = __popcll(__ballot(gone)), n_mask = __popcll(__ballot(mask));
+      past_end += n_gone;
+      masked += n_mask;
+      if (n_gone + n_mask < kWave || w1 <= kWave) break;
+      w1 -= kWave;
+      blk_last = last_window(w1);
+    }
+    n = n_all - past_end;
+    n_main = n - masked;
+  }
+  // pages run by the software-pipelined loop: an even number of unmasked ones
+  const int n_pipe = n_main & ~1;
+
   auto advance = [&](int i) {
     while (i - base >= 64) {
       base += 64;
@@ -961,27 +986,42 @@ __global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_ker
       advance(i + 1);
       step(P1{}, i + 1);
     }
-    // PV of page n_pipe - 1 (odd: its P is PB, its V in v_s1)
+    // K and V of the first remaining page into the buffers that no wave reads
+    // any more, under the PV of page n_pipe - 1 (odd: its P is PB, its V in
+    // v_s1)
+    if (n_pipe < n) {
+      advance(n_pipe);
+      page_to_lds<D, NW, kTileK>(page_ptr(a.k_pool, n_pipe), k_s0, wv, lane);
+      page_to_lds<D, NW, VTILE>(page_ptr(a.v_pool, n_pipe), v_s0, wv, lane);
+    }
     fence_p<NCT>(PB);
     pv_page(PB, v_s1);
     __syncthreads();
+  } else if (n > 0) {
+    page_to_lds<D, NW, kTileK>(page_ptr(a.k_pool, 0), k_s0, wv, lane);
+    page_to_lds<D, NW, VTILE>(page_ptr(a.v_pool, 0), v_s0, wv, lane);
   }
 
   // Remaining pages (the causally masked diagonal ones and an odd leftover),
-  // one at a time without overlap: K and V of the page to LDS, S = K Q^T,
-  // mask, softmax, O += V^T P^T.
-  for (int i = n_pipe; i < n; ++i) {
-    advance(i);
-    page_to_lds<D, NW, kTileK>(page_ptr(a.k_pool, i), k_s0, wv, lane);
-    page_to_lds<D, NW, VTILE>(page_ptr(a.v_pool, i), v_s0, wv, lane);
+  // one at a time: S = K Q^T, mask, softmax, O += V^T P^T from the page's own
+  // buffers (the parameters k_s0, v_s0), while the copies of the next page run
+  // into the other pair.
+  auto rest = [&](int i, uint16_t* k_s0, uint16_t* v_s0, uint16_t* k_next,
+                  uint16_t* v_next) __attribute__((always_inline)) {
+    const int j = id_of(blk_cur, blk_nxt, i);
     copies_landed(k_s0, v_s0);
-    __syncthreads();
+    __syncthreads();   // the page is in, and no wave reads the other buffers any more
+    if (i + 1 < n) {
+      advance(i + 1);
+      page_to_lds<D, NW, kTileK>(page_ptr(a.k_pool, i + 1), k_next, wv, lane);
+      page_to_lds<D, NW, VTILE>(page_ptr(a.v_pool, i + 1), v_next, wv, lane);
+    }
     if (i >= n_main) {
       // The tokens of a sequence's last page past its end are not part of it
       // and may hold anything: their weights are exactly 0, so their V
       // entries (the last `past` keys of the page) are zeroed to keep
       // 0 * NaN out of O (their K scores are masked).
-      const int past = kPage * id_of(blk_cur, blk_nxt, i) + kPage - (cl + a.C);
+      const int past = kPage * j + kPage - (cl + a.C);
       if (past > 0) {
         for (int x = t; x < past * D; x += 64 * NW) {
           const int r = x / past, key = kPage - past + x % past;   // r: the d index
@@ -994,7 +1034,6 @@ __global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_ker
     qk_page(SA, k_s0);
     fence_s<NCT>(SA);
     if (i >= n_main) {
-      const int j = id_of(blk_cur, blk_nxt, i);
 #pragma unroll
       for (int c = 0; c < NCT; ++c) {
         const int lim = qpos[c] - kPage * j;
@@ -1047,7 +1086,10 @@ __global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_ker
     }
     fence_p<NCT>(PA);
     pv_page(PA, v_s0);
-    __syncthreads();
+  };
+  for (int i = n_pipe; i < n; i += 2) {
+    rest(i, k_s0, v_s0, k_s1, v_s1);
+    if (i + 1 < n) rest(i + 1, k_s1, v_s1, k_s0, v_s0);
   }
   fence_o<AG>(o);
 
