@@ -267,6 +267,12 @@ ca_status ca_estimate_tables(const ca_problem* p, const uint16_t* q, const uint1
  *    num_splits: 1 = one pass per query tile; > 1 = the table of each row is
  *    cut into that many consecutive pieces whose partial results are merged
  *    by log-sum-exp (needs workspace); 0 = let the library choose:
+ *      - when fewer than 32 query tiles share at most 64 table rows and there
+ *        is work for every CU (about 4 expected pages each) and the workspace
+ *        holds ca_attention_workspace_bytes(p, group_size, 0): one workgroup
+ *        per CU, each running an equal share of the pages, computed on the GPU
+ *        from the table lengths (not where uniform splits are as even: see
+ *        attn_shares in csrc/kernels.hpp); a second launch merges the pieces;
  *      - when the query tiles fill the GPU, B * G is a multiple of 8 and the
  *        workspace holds ca_attention_workspace_bytes(p, group_size, 0):
  *        every table row is cut in two at a point computed on the GPU from
@@ -282,7 +288,8 @@ ca_status ca_estimate_tables(const ca_problem* p, const uint16_t* q, const uint1
  *    partial result from the workspace and writes the tile's output rows.
  *    It learns that it is second from one counter per tile in the
  *    workspace, which each launch tags with its own 56-bit value.  Uniform
- *    splits (num_splits > 1) are merged by a second launch on the stream.
+ *    splits (num_splits > 1) and equal shares are merged by a second launch on
+ *    the stream.
  *    Either way the workspace needs no clearing and may hold anything on
  *    entry (a launch leaves its counters at zero), and two launches that run
  *    at the same time must not share a workspace.

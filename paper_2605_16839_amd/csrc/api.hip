@@ -115,7 +115,7 @@ int auto_splits(const ca::Dims& d, int group_size, size_t ws_bytes, bool have_ws
   int s = (target + base - 1) / base;
   const int max_by_len = d.max_nkb / 4 > 1 ? d.max_nkb / 4 : 1;
   if (s > max_by_len) s = max_by_len;
-  if (s > 16) s = 16;
+  if (s > ca::kMaxUniformSplits) s = ca::kMaxUniformSplits;
   while (s > 1 && ca::attn_ws_bytes(d, s) > ws_bytes) --s;
   return s < 1 ? 1 : s;
 }
@@ -335,10 +335,19 @@ ca_status run_attention(const ca_problem* p, const uint16_t* q, const uint16_t* 
     return fail(CA_ERR_SHAPE, "num_splits %d out of range [0, 64]", num_splits);
   int splits = num_splits;
   bool xcd = false;
+  ca::AttnShares shares;
   if (splits == 0) {
-    xcd = xcd_balance_ok(d, p, group_size, table_mode, dense) && ws != nullptr &&
+    // equal shares per CU; with too little workspace (or an unaligned one) the
+    // launches below, as they take it
+    if (table_mode != ca::kTablesPerQTile && ws != nullptr &&
+        reinterpret_cast<uintptr_t>(ws) % 16 == 0) {
+      shares = ca::attn_shares(d, group_size, p->cached_len_host, dense);
+      if (shares.on && ws_bytes < ca::attn_shares_ws_bytes(d, group_size, shares))
+        shares.on = false;
+    }
+    xcd = !shares.on && xcd_balance_ok(d, p, group_size, table_mode, dense) && ws != nullptr &&
           ws_bytes >= ca::attn_xcd_ws_bytes(d, group_size);
-    splits = xcd ? 2 : auto_splits(d, group_size, ws_bytes, ws != nullptr, table_mode);
+    splits = shares.on ? 1 : xcd ? 2 : auto_splits(d, group_size, ws_bytes, ws != nullptr, table_mode);
   }
   if (splits > 1) {
     const size_t need = ca::attn_ws_bytes(d, splits);
@@ -362,6 +371,7 @@ ca_status run_attention(const ca_problem* p, const uint16_t* q, const uint16_t* 
   L.sm_scale = sm_scale;
   L.splits = splits;
   L.xcd_balanced = xcd;
+  L.shares = shares;
   L.ws = ws;
   L.dense = dense;
   L.table_mode = table_mode;
@@ -704,7 +714,14 @@ size_t ca_attention_workspace_bytes(const ca_problem* p, int32_t group_size, int
     const size_t bal = xcd_balance_ok(d, p, group_size, ca::kTablesPerGroup, false)
                            ? ca::attn_xcd_ws_bytes(d, group_size)
                            : 0;
-    return bal > uni ? bal : uni;
+    size_t need = bal > uni ? bal : uni;
+    // or for equal shares per CU, of the selected tables or the dense ones
+    for (const bool dense : {false, true}) {
+      const size_t sh = ca::attn_shares_ws_bytes(
+          d, group_size, ca::attn_shares(d, group_size, p->cached_len_host, dense));
+      need = sh > need ? sh : need;
+    }
+    return need;
   }
   return ca::attn_ws_bytes(d, s);
 }

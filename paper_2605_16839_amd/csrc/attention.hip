@@ -42,7 +42,11 @@
 //   * the XCD-balanced split's two pieces are merged inside the kernel: the
 //     second piece of a query tile to finish (an arrival counter per tile)
 //     reads the other's partial result and writes the output rows; uniform
-//     splits are merged by combine_kernel.
+//     splits are merged by combine_kernel;
+//   * where query tiles and table rows would leave CUs idle (short or odd
+//     chunks, few or unequal rows), one workgroup per CU runs an equal share of
+//     all pages, a few pieces of rows (balanced_attention_kernel, the shares in
+//     kernels.hpp); combine_pieces_kernel merges them.
 #include <atomic>
 #include <chrono>
 #include <random>
@@ -95,9 +99,12 @@ struct AttnArgs {
   // run whole as piece 0; -2 = not cut, run whole as piece 1
   int32_t* split_at;
   int rows_per_unit;   // table rows that read one KV head's pages together
+  AttnShares shares;   // balanced launch only (balanced_attention_kernel)
+  int4* pieces;        // balanced launch: {j0, pieces, per_slab} of every (row, tile)
 };
 
-constexpr int kXcds = 8;   // MI355X: 8 accelerator complex dies, 32 CUs and one L2 each
+constexpr int kXcds = kAttnXcds;   // MI355X: 8 accelerator complex dies, 32 CUs and one L2 each
+constexpr int kCusPerXcd = kAttnCusPerXcd;
 
 // 64-bit lane exchanges as two 32-bit ones.
 __device__ __forceinline__ long long shfl_xor_i64(long long v, int mask) {
@@ -472,8 +479,77 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-template <int D, int NW, int NCT, bool DENSE, int VL>
-__global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_kernel(const AttnArgs a) {
+// One CU's walk over its pieces of a balanced launch (kernels.hpp).  Every lane
+// of every wave computes the same walk; lanes hold the table rows.
+template <bool DENSE>
+struct ShareWalk {
+  const int x, c;       // XCD and CU
+  int t, r_next;        // the tile and the first row not yet run; t < 0: done
+  // the current piece
+  int row, tile, e0, e1, ordinal;
+  PieceList list;
+
+  __device__ __forceinline__ ShareWalk(int bid, const AttnArgs& a)
+      : x(bid % kXcds), c(bid / kXcds), t(c), r_next(0) {
+    const AttnShares& s = a.shares;
+    const int n_main = s.n * s.s_main;
+    if (c < n_main) t = c % s.n;
+    else t = (int)share_div((c - n_main) * s.n, s.left);   // (c < n_main when left is 0)
+  }
+
+  // Moves to the next piece; false when there is none left.
+  __device__ __forceinline__ bool next(const AttnArgs& a, int lane) {
+    const AttnShares& s = a.shares;
+    const int R = a.B * a.G, n_main = s.n * s.s_main;
+    const int lr = lane < R ? lane : R - 1;
+    if (t < 0) return false;
+    const int cl = a.cached_len[lr / a.G];
+    int len;
+    if (DENSE) len = blocks_for(cl + a.C);
+    else len = a.kv_indptr[lr + 1] - a.kv_indptr[lr];
+    while (t >= 0) {
+      const int w = share_visible(len, cl, a.C, t, s.query_tile, kPage);
+      const int cost = lane < R ? w + s.overhead : 0;
+      const ShareRow mine = {wave_inclusive_scan(cost) - cost, w, len, s.overhead};
+      const ShareLine line = share_line(s, __builtin_amdgcn_readlane(mine.A + cost, 63), t);
+      // this CU's interval of the tile's line: a main segment, or its part of
+      // the last one (if there is one)
+      const bool main_cu = c < n_main;
+      const int e = c - n_main;
+      const unsigned i = main_cu ? c / s.n : s.s_main + (e * s.n > t * s.left ? 1 : 0);
+      const int lo = i < line.per ? (int)share_cut(line, x, i) : 0;
+      const int hi = i < line.per ? (int)share_cut(line, x, i + 1) : -1;
+      const unsigned long long meet = __ballot(lane < R && lane >= r_next && mine.meets(lo, hi));
+      const int t_next = !main_cu && (t + 1) * s.left < (e + 1) * s.n ? t + 1 : -1;
+      if (meet != 0) {
+        row = __builtin_ctzll(meet);
+        const ShareRow r = {__builtin_amdgcn_readlane(mine.A, row),
+                            __builtin_amdgcn_readlane(w, row),
+                            __builtin_amdgcn_readlane(len, row), s.overhead};
+        tile = t;
+        e0 = lo >= r.first() ? r.entry(lo) : 0;
+        e1 = hi <= r.last() ? r.entry(hi) : r.len;
+        list.j0 = (int)share_cuts_upto(line, r.first() - 1);
+        list.pieces = (int)share_cuts_upto(line, r.last()) - list.j0 + 1;
+        list.per_slab = (int)line.per;
+        list.tile = t;
+        ordinal = (int)(x * line.per + i) - list.j0;
+        r_next = row + 1;
+        if ((meet & (meet - 1)) == 0) {   // the tile's last row here
+          r_next = 0;
+          t = t_next;
+        }
+        return true;
+      }
+      r_next = 0;
+      t = t_next;
+    }
+    return false;
+  }
+};
+
+template <int D, int NW, int NCT, bool DENSE, int VL, bool BAL>
+__device__ __forceinline__ void attend(const AttnArgs& a) {
   constexpr bool AG = NCT == 4;        // O^T and Q^T in AGPRs (one wave per SIMD)
   constexpr bool VTR = VL == kVTransposed;
   constexpr int VTILE = VTR ? kTileVT : kTileVR;
@@ -497,71 +573,40 @@ __global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_ker
   __shared__ __attribute__((aligned(1024))) uint16_t v_s0[PAGE];
   __shared__ __attribute__((aligned(1024))) uint16_t v_s1[PAGE];
 
-  const int t = threadIdx.x;
-  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int lane = t & 63;
   // The two waves that share a SIMD run the same slot schedule and meet at
   // every page barrier.  Half the waves (one per SIMD when the waves of a
   // workgroup are placed round-robin over the 4 SIMDs) get the higher issue
   // priority: that wave runs ahead within the step and the other fills the
   // gaps it leaves (0.4-0.6% at 128K in same-box A/B timings).
-  if (NCT == 2 && wv < NW / 2) __builtin_amdgcn_s_setprio(1);
+  if (NCT == 2 && __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < NW / 2)
+    __builtin_amdgcn_s_setprio(1);
+
+  ShareWalk<DENSE> walk(blockIdx.x, a);   // balanced launch
+
+  // One piece: the entries of table row rowid that piece sp (or the walk's
+  // current piece) holds, for query tile qt.
+  auto piece = [&](const AttnArgs& a, int t, int rowid, int qt,
+                   int sp) __attribute__((always_inline)) {
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int lane = t & 63;
   const int col = lane & 15;           // query column within a 16-column tile
   const int grp = lane >> 4;           // lane group: keys 4*grp .. of each 16-key tile
-
-  int bid = blockIdx.x;
-  const int nwg = gridDim.x;
-  if ((nwg & 7) == 0) bid = (bid & 7) * (nwg >> 3) + (bid >> 3);
-  int sp, qt, rowid;
-  if (a.split_at != nullptr) {
-    // XCD x (logical workgroups [x, x+1) * nwg/8) holds the rows r with
-    // r % 8 = x (group x of every sequence when G = 8); it first runs piece 0
-    // of its own rows' tiles, then piece 1 of the previous XCD's rows' tiles:
-    // each piece is read by all tiles of its row on one XCD, in step, through
-    // that XCD's L2
-    const int per_xcd = nwg / kXcds, own = per_xcd / 2;
-    const int x = bid / per_xcd;
-    int j = bid % per_xcd;
-    sp = j < own ? 0 : 1;
-    if (sp) j -= own;
-    rowid = (sp ? x + kXcds - 1 : x) % kXcds + kXcds * (j / a.n_qtiles);
-    qt = j % a.n_qtiles;
-    if (sp) qt = a.n_qtiles - 1 - qt;   // second pieces in mirrored tile order
-  } else {
-    // XCD x holds the units u with u % 8 = x when the units spread evenly (a
-    // unit = the table rows that read one KV head's pages: one group row, or
-    // the heads of one KV group in the per-(head, Q-block) layout), so that
-    // sequences of different lengths share every XCD; otherwise rows in order
-    const int per_row = a.splits * a.n_qtiles;
-    const int U = a.rows_per_unit;
-    const int units = nwg / per_row / U;
-    int rest;
-    if ((nwg & 7) == 0 && units % kXcds == 0) {
-      const int per_xcd = nwg / kXcds, per_unit = U * per_row;
-      const int x = bid / per_xcd, j = bid % per_xcd;
-      rowid = (x + kXcds * (j / per_unit)) * U + (j % per_unit) / per_row;
-      rest = j % per_row;
-    } else {
-      rowid = bid / per_row;
-      rest = bid % per_row;
-    }
-    sp = rest % a.splits;
-    qt = rest / a.splits;
-  }
   const int b = rowid / a.G;
   const int g = rowid % a.G;
   const int gs = a.group_size;
-  const int QT = ROWS / gs;            // chunk queries per tile
+  const int QT = BAL ? a.shares.query_tile : ROWS / gs;   // chunk queries per tile
   const int q0 = qt * QT;
   const int q_end = q0 + QT < a.C ? q0 + QT : a.C;   // the last tile may be partial
   int head[NCT], tq[NCT];
   bool valid[NCT];
 #pragma unroll
   for (int c = 0; c < NCT; ++c) {
-    const int r = wv * 16 * NCT + 16 * c + col;
+    int r = wv * 16 * NCT + 16 * c + col;
+    const bool in_tile = !BAL || r < gs * QT;
+    if (!in_tile) r = 0;
     head[c] = g * gs + r / QT;
     tq[c] = q0 + r % QT;
-    valid[c] = tq[c] < a.C;
+    valid[c] = in_tile && tq[c] < a.C;
     if (!valid[c]) tq[c] = a.C - 1;    // computes a copy of a real row, never stored
   }
   const int kvh = (g * gs) / (a.Hq / a.Hkv);
@@ -584,7 +629,11 @@ __global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_ker
   }
   int e0, e1;
   bool whole = a.splits == 1;   // the piece is the whole row: final output
-  if (a.split_at != nullptr) {
+  if constexpr (BAL) {
+    e0 = walk.e0;
+    e1 = walk.e1;
+    whole = walk.list.pieces == 1;
+  } else if (a.split_at != nullptr) {
     int cut = xcd_cut<DENSE>(a, rowid);
     if (sp == 0 && qt == 0 && t == 0) a.split_at[rowid] = cut;   // a record of the schedule
     if (cut < 0) {              // the row is not cut: one piece runs it, the other nothing
@@ -1114,6 +1163,11 @@ __global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_ker
     }
     if (a.lse != nullptr && grp == 0) a.lse[qrow_idx[c]] = lse_row;
   };
+  if constexpr (BAL) {
+    if (walk.ordinal == 0 && t == 0)   // for the merge launch
+      a.pieces[rowid * a.n_qtiles + qt] = make_int4(walk.list.j0, walk.list.pieces,
+                                                    walk.list.per_slab, 0);
+  }
   if (whole) {
 #pragma unroll
     for (int c = 0; c < NCT; ++c) {
@@ -1130,6 +1184,24 @@ __global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_ker
 
   // One piece of a split row tile: its result is the normalised partial
   // output o * inv with its log-sum-exp.
+  if constexpr (BAL) {
+    // as the registers lie: fragment (x, c) of a wave is 64 float4, so that a
+    // store writes 1 KB in one run and combine_pieces_kernel reads it so (rows
+    // of D floats made 16 runs of 64 bytes of it)
+    const size_t slot = walk.list.slot(walk.ordinal, a.shares);
+    float4* po = reinterpret_cast<float4*>(a.part_o) + (slot * NW + wv) * (NDT * NCT * 64) + lane;
+    float* pl = a.part_lse + slot * ROWS + wv * 16 * NCT + col;
+#pragma unroll
+    for (int c = 0; c < NCT; ++c) {
+      if (__ballot(valid[c]) == 0) continue;
+#pragma unroll
+      for (int x = 0; x < NDT; ++x)
+        po[(x * NCT + c) * 64] = make_float4(o[x][c][0] * inv[c], o[x][c][1] * inv[c],
+                                             o[x][c][2] * inv[c], o[x][c][3] * inv[c]);
+      if (grp == 0) pl[16 * c] = lse_val[c];
+    }
+    return;
+  }
   const size_t nrows = (size_t)a.B * a.Hq * a.C;
   auto store_part = [&]() {
 #pragma unroll
@@ -1234,6 +1306,93 @@ __global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_ker
     }
     store_out(c, acc, wsum > 0.f ? 1.0f / wsum : 0.f, wsum > 0.f ? mx + logf(wsum) : -INFINITY);
   }
+  };
+
+  if constexpr (BAL) {
+    for (;;) {
+      // the thread id and the arguments' address go through an empty asm, so
+      // that nothing a piece derives from them is kept in registers across
+      // the pieces: the pipelined steps need every register
+      int tid = threadIdx.x;
+      auto* args = (const __attribute__((address_space(4))) AttnArgs*)
+          __builtin_amdgcn_kernarg_segment_ptr();
+      asm volatile("" : "+v"(tid), "+s"(args));
+      const AttnArgs& aa = *(const AttnArgs*)args;
+      if (!walk.next(aa, tid & 63)) break;
+      piece(aa, tid, walk.row, walk.tile, 0);
+      __syncthreads();   // no wave reads the tiles (or the merge flag) of this piece any more
+    }
+  } else {
+    int bid = blockIdx.x;
+    const int nwg = gridDim.x;
+    if ((nwg & 7) == 0) bid = (bid & 7) * (nwg >> 3) + (bid >> 3);
+    int sp, qt, rowid;
+    if (a.split_at != nullptr) {
+      // XCD x (logical workgroups [x, x+1) * nwg/8) holds the rows r with
+      // r % 8 = x (group x of every sequence when G = 8); it first runs piece 0
+      // of its own rows' tiles, then piece 1 of the previous XCD's rows' tiles:
+      // each piece is read by all tiles of its row on one XCD, in step, through
+      // that XCD's L2
+      const int per_xcd = nwg / kXcds, own = per_xcd / 2;
+      const int x = bid / per_xcd;
+      int j = bid % per_xcd;
+      sp = j < own ? 0 : 1;
+      if (sp) j -= own;
+      rowid = (sp ? x + kXcds - 1 : x) % kXcds + kXcds * (j / a.n_qtiles);
+      qt = j % a.n_qtiles;
+      if (sp) qt = a.n_qtiles - 1 - qt;   // second pieces in mirrored tile order
+    } else {
+      // XCD x holds the units u with u % 8 = x when the units spread evenly (a
+      // unit = the table rows that read one KV head's pages: one group row, or
+      // the heads of one KV group in the per-(head, Q-block) layout), so that
+      // sequences of different lengths share every XCD; otherwise rows in order
+      const int per_row = a.splits * a.n_qtiles;
+      const int U = a.rows_per_unit;
+      const int units = nwg / per_row / U;
+      int rest;
+      if ((nwg & 7) == 0 && units % kXcds == 0) {
+        const int per_xcd = nwg / kXcds, per_unit = U * per_row;
+        const int x = bid / per_xcd, j = bid % per_xcd;
+        rowid = (x + kXcds * (j / per_unit)) * U + (j % per_unit) / per_row;
+        rest = j % per_row;
+      } else {
+        rowid = bid / per_row;
+        rest = bid % per_row;
+      }
+      sp = rest % a.splits;
+      qt = rest / a.splits;
+    }
+    piece(a, threadIdx.x, rowid, qt, sp);
+  }
+}
+
+// One workgroup per piece of a table row (the whole row, a uniform split, or
+// one of the two pieces of the XCD-balanced split).
+template <int D, int NW, int NCT, bool DENSE, int VL>
+__global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_kernel(const AttnArgs a) {
+  attend<D, NW, NCT, DENSE, VL, false>(a);
+}
+
+// One workgroup per CU, each running an equal share of the launch's pages
+// (ShareWalk; the shares are described in kernels.hpp).  What bounded such
+// launches was the CUs left idle: 184 tiles in two uniform splits are 368
+// pieces, two rounds of 256 CUs for 1.4 rounds of work; one tile per row in 16
+// splits uses half the CUs; rows of unequal length leave whole XCDs waiting.
+// Against those launches (one box, attention and merge, D = 128 unless said):
+//   1451 tokens over 50001, 0.3 listed       429 -> 347 us
+//   1200 tokens over 8192, dense             240 -> 178 us
+//   two rows per XCD, 184 / 84 pages, D = 64 196 -> 168 us
+//   64 tokens over 16384, dense               50 -> 40 us
+//   1024 tokens over 129024, 0.3 listed      561 -> 547 us
+// A piece costs about 12 us besides its pages (walk 2.5, prologue 4.5, pages
+// outside the pipeline 3, storing 128 KB of partial results while 255 other
+// CUs do 4), which is why short rows are not cut and few pieces are made.
+// Merging inside the launch with arrival counters, as the XCD-balanced split
+// does, doubled the time of short launches: each counter needs a fence that
+// writes back or invalidates an XCD's whole L2, and all pieces end at once.
+template <int D, int NW, int NCT, bool DENSE, int VL>
+__global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void balanced_attention_kernel(const AttnArgs a) {
+  attend<D, NW, NCT, DENSE, VL, true>(a);
 }
 
 // Copy arm (Sec. 4.4): pack the selected K and V pages of every table row into
@@ -1391,6 +1550,75 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
   if (lse != nullptr && sub == 0) lse[row] = wsum > 0.f ? mx + logf(wsum) : -INFINITY;
 }
 
+// Merge of the pieces of a balanced launch: lse = log sum_i exp(lse_i),
+// out = sum_i exp(lse_i - lse) o_i, pieces in order.  One wave per fragment of
+// a tile (16 rows x 16 d, as the attention kernel's registers lie): each piece's
+// fragment is one 1 KB load, up to kCombineInFlight pieces in flight.  A tile
+// that one piece ran whole has its output already.
+template <int D>
+__global__ __launch_bounds__(256) void combine_pieces_kernel(const AttnArgs a) {
+  constexpr int NDT = D / 16, FRAGS = NDT * kColTiles, NW = kWavesGroup;
+  constexpr int ROWS = 16 * kColTiles * NW;
+  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);   // (row, tile, wave, fragment)
+  const int f = unit % FRAGS, wv = (unit / FRAGS) % NW, tile = unit / (FRAGS * NW);
+  const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
+  const int n = a.n_qtiles, r = tile / n, t = tile - r * n;
+  const int4 d = a.pieces[tile];
+  if (d.y == 1) return;
+  const PieceList list = {d.x, d.y, d.z, t};
+  // the fragment's rows, as in the attention kernel
+  const int QT = a.shares.query_tile, row = wv * 16 * kColTiles + 16 * (f % kColTiles) + col;
+  const int b = r / a.G, head = (r - b * a.G) * a.group_size + row / QT;
+  const int tq = t * QT + row % QT;
+  const bool valid = row < a.group_size * QT && tq < a.C;
+  if (__ballot(valid) == 0) return;
+  auto slot = [&](int i) {
+    return (size_t)list.slot(i, a.shares);
+  };
+  float mx = -INFINITY, wsum = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int i0 = 0; i0 < list.pieces; i0 += kCombineInFlight) {
+    // a batch of pieces; a batch with a higher maximum rescales what came before
+    float l[kCombineInFlight], m_new = mx;
+    float4 v[kCombineInFlight];
+#pragma unroll
+    for (int k = 0; k < kCombineInFlight; ++k) {
+      if (i0 + k < list.pieces) {
+        const size_t sl = slot(i0 + k);
+        l[k] = a.part_lse[sl * ROWS + row];
+        v[k] = reinterpret_cast<const float4*>(a.part_o)[(sl * NW + wv) * (FRAGS * 64) + f * 64 + lane];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kCombineInFlight; ++k)
+      if (i0 + k < list.pieces) m_new = fmaxf(m_new, l[k]);
+    if (m_new == -INFINITY) continue;
+    const float keep = mx == -INFINITY ? 0.f : expf(mx - m_new);
+    mx = m_new;
+    wsum *= keep;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] *= keep;
+#pragma unroll
+    for (int k = 0; k < kCombineInFlight; ++k) {
+      if (i0 + k >= list.pieces || l[k] == -INFINITY) continue;
+      const float wgt = expf(l[k] - mx);
+      wsum += wgt;
+      acc[0] = fmaf(wgt, v[k].x, acc[0]);
+      acc[1] = fmaf(wgt, v[k].y, acc[1]);
+      acc[2] = fmaf(wgt, v[k].z, acc[2]);
+      acc[3] = fmaf(wgt, v[k].w, acc[3]);
+    }
+  }
+  if (!valid) return;
+  const float inv = wsum > 0.f ? 1.0f / wsum : 0.f;
+  uint2 pk;
+  pk.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
+  pk.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
+  uint16_t* orow = a.out + (((size_t)b * a.C + tq) * a.Hq + head) * D;
+  *reinterpret_cast<uint2*>(orow + 16 * (f / kColTiles) + 4 * grp) = pk;
+  if (a.lse != nullptr && f < kColTiles && grp == 0)
+    a.lse[((size_t)b * a.Hq + head) * a.C + tq] = wsum > 0.f ? mx + logf(wsum) : -INFINITY;
+}
+
 int attn_rows_per_workgroup(int table_mode) {
   return 16 * kColTiles * (table_mode == kTablesPerQTile ? kWavesQTile : kWavesGroup);
 }
@@ -1432,6 +1660,29 @@ size_t attn_xcd_ws_bytes(const Dims& d, int group_size) {
          (size_t)attn_base_workgroups(d, group_size, kTablesPerGroup) * 8;
 }
 
+AttnShares attn_shares(const Dims& d, int group_size, const int32_t* cached_len_host, bool dense) {
+  const int QT = attn_query_tile(group_size, kTablesPerGroup);
+  if (QT < 1) return {};   // not a tile the kernels run (refused before a launch)
+  return attn_shares(d.B, d.Hq / group_size, d.C, (d.C + QT - 1) / QT, QT, d.D, kPage,
+                     cached_len_host, dense);
+}
+
+// Workspace of a balanced launch: the partial results and log-sum-exps of two
+// pieces per interval (fp32), then the piece list of every (row, tile).
+static size_t shares_partial_rows(const AttnShares& s) {
+  return (size_t)kXcds * s.slots_per_slab * 2 * attn_rows_per_workgroup(kTablesPerGroup);
+}
+
+static size_t shares_lists_at(const Dims& d, const AttnShares& s) {
+  return (shares_partial_rows(s) * (d.D + 1) * sizeof(float) + 15) & ~(size_t)15;
+}
+
+size_t attn_shares_ws_bytes(const Dims& d, int group_size, const AttnShares& s) {
+  return s.on ? shares_lists_at(d, s) +
+                    (size_t)attn_base_workgroups(d, group_size, kTablesPerGroup) * sizeof(int4)
+              : 0;
+}
+
 // A tag per launch for the arrival counters: consecutive values from a
 // per-process random start, kept below 2^56 and never 0.  A counter left with
 // another tag (an earlier launch, or whatever the workspace held) counts 0.
@@ -1452,6 +1703,15 @@ template <int D, int NW, int VL>
 static void launch_kernel(const AttnArgs& a, bool dense, int nwg, hipStream_t st) {
   if (dense) paged_attention_kernel<D, NW, kColTiles, true, VL><<<nwg, 64 * NW, 0, st>>>(a);
   else paged_attention_kernel<D, NW, kColTiles, false, VL><<<nwg, 64 * NW, 0, st>>>(a);
+}
+
+template <int D, int VL>
+static void launch_balanced(const AttnArgs& a, bool dense, hipStream_t st) {
+  constexpr int NW = kWavesGroup, grid = kXcds * kCusPerXcd;
+  if (dense) balanced_attention_kernel<D, NW, kColTiles, true, VL><<<grid, 64 * NW, 0, st>>>(a);
+  else balanced_attention_kernel<D, NW, kColTiles, false, VL><<<grid, 64 * NW, 0, st>>>(a);
+  const int units = a.B * a.G * a.n_qtiles * NW * (D / 16) * kColTiles;
+  combine_pieces_kernel<D><<<units / 4, 256, 0, st>>>(a);
 }
 
 template <int D, int NW>
@@ -1502,6 +1762,19 @@ hipError_t launch_attention(const Dims& d, const AttnLaunch& L, hipStream_t st) 
     a.tag = next_arrival_tag();
   }
   const bool qtile = L.table_mode == kTablesPerQTile;
+  a.pieces = nullptr;
+  if (L.shares.on) {
+    a.shares = L.shares;
+    a.part_o = static_cast<float*>(L.ws);
+    a.part_lse = a.part_o + shares_partial_rows(a.shares) * d.D;
+    a.pieces = reinterpret_cast<int4*>(static_cast<char*>(L.ws) + shares_lists_at(d, a.shares));
+    const bool vt = L.v_layout == kVTransposed;
+    if (d.D == 128) vt ? launch_balanced<128, kVTransposed>(a, L.dense, st)
+                       : launch_balanced<128, kVTokenMajor>(a, L.dense, st);
+    else vt ? launch_balanced<64, kVTransposed>(a, L.dense, st)
+            : launch_balanced<64, kVTokenMajor>(a, L.dense, st);
+    return hipGetLastError();
+  }
   if (d.D == 128) {
     if (qtile) launch_layout<128, kWavesQTile>(a, L.dense, L.v_layout, nwg, st);
     else launch_layout<128, kWavesGroup>(a, L.dense, L.v_layout, nwg, st);

@@ -56,6 +56,221 @@ constexpr int kTablesPerGroup = 0;   // row b*G + g, entries translated by page_
 constexpr int kTablesPerQTile = 1;   // row (b*Hq + h)*n_qtiles + tile (block-sparse arm)
 constexpr int kTablesPacked = 2;     // per-group rows; page of entry p is p (copy arm)
 
+// ---------------------------------------------------------------------------
+// Equal shares of a launch's pages, one per CU: the arithmetic of the balanced
+// attention launch (plain integers, the same on host and device).
+//
+// For a query tile t, the table rows r = 0 .. R-1 laid end to end form a line
+// of length T(t), row r on [A_r, A_r + o + w_r): o is what a piece's start and
+// end cost, in entries, and w_r the number of the row's entries the tile can
+// see if the row lists the chunk's own blocks (at least 1, so that every row
+// has a piece that writes its output, and never more than the true count, so
+// that no piece is left out; the piece holding the last of them runs on to the
+// row's end and drops what the tile cannot see).  XCD x takes the slab
+// [x T/8, (x+1) T/8) of the line, and its 32 CUs share the n < 32 tiles' slabs:
+// a slab is cut into s_main = 32 / n main segments of equal length and, when
+// n * s_main < 32, a shorter last one.  CU i*n + t runs main segment i of tile
+// t.  The m = 32 - n*s_main < n CUs left over share the last segments of all
+// tiles, laid end to end and cut into m equal parts (so a tile's last segment
+// is cut at most once more); a last segment is as long as makes a part and the
+// cost of its pieces equal to a main segment and its piece.  All tiles of a
+// segment walk the same entries in step, which the XCD's 4 MB L2 needs for long
+// rows.
+//
+// Where a cut meets a row it takes effect at an even entry (the kernel
+// pipelines pairs of pages), or not at all when it falls on the row's first o
+// or so near an end that the short piece would cost more than it moves: the
+// row then starts, or ends, with the cut (ShareRow).  Interval J of a tile's
+// line lies between its cuts J-1 and J.  A row's pieces are the intervals j0 ..
+// j0+P-1 that meet it, in entry order (one between two cuts that take effect at
+// the same entry is empty).
+// ---------------------------------------------------------------------------
+constexpr int kAttnXcds = 8;         // MI355X: 8 dies of 32 CUs, one L2 each
+constexpr int kAttnCusPerXcd = 32;
+constexpr int kSharesMaxRows = 64;   // one table row per lane
+
+struct AttnShares {
+  bool on = false;
+  int n = 1;               // query tiles
+  int s_main = 1;          // main segments per slab
+  int left = 0;            // CUs left over (m above)
+  int overhead = 0;        // cost of a piece's start and end, in entries
+  int query_tile = 0;      // chunk queries per tile
+  int slots_per_slab = 0;  // intervals of one slab over all tiles
+};
+
+// a / b for a quotient below 2^20 (one step of correction on the float one).
+__host__ __device__ __forceinline__ unsigned share_div(unsigned a, unsigned b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  unsigned q = (unsigned)((float)a * __builtin_amdgcn_rcpf((float)b));
+  int r = (int)(a - q * b);
+  if (r < 0) --q, r += (int)b;
+  if (r >= (int)b) ++q;
+  return q;
+#else
+  return a / b;
+#endif
+}
+
+// Cuts of tile t's line, of length T: interval i < per of slab x begins at
+// share_cut(x, i).
+struct ShareLine {
+  unsigned T, S;
+  unsigned last;    // length of a slab's last segment (0: there is none)
+  unsigned inner;   // where in it another cut lies (0: there is none)
+  unsigned per;     // intervals per slab
+};
+
+// The left-over CU that begins inside the last segment of tile t, or begins
+// with the next tile's.
+__host__ __device__ __forceinline__ unsigned share_next_left(const AttnShares& s, unsigned t) {
+  return share_div(t * s.left, s.n) + 1;
+}
+
+__host__ __device__ __forceinline__ ShareLine share_line(const AttnShares& s, unsigned T, unsigned t) {
+  ShareLine l = {T, (unsigned)s.s_main, 0, 0, (unsigned)s.s_main};
+  if (s.left > 0) {
+    // main + overhead = (n / m) last + pieces * overhead, where a left-over CU
+    // has n / m pieces, and one more when its part begins inside a tile;
+    // s_main * main + last = T / 8
+    const int m = s.left, n = s.n, begun = n % m != 0 ? m - 1 : 0;
+    const int room = (int)(T / kAttnXcds) * m - s.s_main * s.overhead * (n + begun - m);
+    if (room > 0) l.last = share_div((unsigned)room, (unsigned)(s.s_main * n + m));
+    if (l.last > 0) {
+      ++l.per;
+      const unsigned at = share_next_left(s, t) * n - t * m;   // of m parts of the segment
+      if (at < (unsigned)m) {
+        l.inner = share_div(l.last * at + m - 1, m);
+        ++l.per;
+      }
+    }
+  }
+  return l;
+}
+
+__host__ __device__ __forceinline__ unsigned share_slab(const ShareLine& l, unsigned x) {
+  return (l.T * x + kAttnXcds - 1) / kAttnXcds;
+}
+// Combined length of the main segments of slab [b0, b1).
+__host__ __device__ __forceinline__ unsigned share_main(const ShareLine& l, unsigned b0, unsigned b1) {
+  return b1 - b0 > l.last ? b1 - b0 - l.last : 0;
+}
+
+__host__ __device__ __forceinline__ unsigned share_cut(const ShareLine& l, unsigned x, unsigned i) {
+  const unsigned b0 = share_slab(l, x), b1 = share_slab(l, x + 1);
+  if (i >= l.per) return b1;
+  const unsigned main = share_main(l, b0, b1);
+  if (i > l.S) {
+    const unsigned cut = b0 + main + l.inner;
+    return cut < b1 ? cut : b1;
+  }
+  return b0 + share_div(main * i + l.S - 1, l.S);
+}
+
+// Number of cuts at or before position p (< T).
+__host__ __device__ __forceinline__ unsigned share_cuts_upto(const ShareLine& l, unsigned p) {
+  unsigned x = share_div(kAttnXcds * p, l.T);
+  if (x < kAttnXcds - 1 && share_slab(l, x + 1) <= p) ++x;
+  const unsigned b0 = share_slab(l, x), main = share_main(l, b0, share_slab(l, x + 1));
+  // cut i <= p - b0  <=>  main * i <= S (p - b0)
+  unsigned i = l.last > 0 ? l.S : l.S - 1;
+  if (main > 0) {
+    const unsigned q = share_div(l.S * (p - b0), main);
+    i = q < i ? q : i;
+  }
+  if (l.inner > 0 && p >= b0 + main + l.inner) i = l.S + 1;
+  return x * l.per + i;
+}
+
+// One row of the line: len entries, w of them counted, on [A, A + o + w).
+struct ShareRow {
+  int A, w, len, o;
+  __host__ __device__ __forceinline__ int near() const { return w / 4 < o ? w / 4 : o; }   // too short for a piece
+  // The first and the last position at which a cut divides the row.
+  __host__ __device__ __forceinline__ int first() const { return A + o + near() + 1; }
+  __host__ __device__ __forceinline__ int last() const { return A + o + w - near() - 1; }
+  __host__ __device__ __forceinline__ bool meets(int lo, int hi) const { return hi >= first() && lo <= last(); }
+  // The entry at which a cut at or after first() takes effect.
+  __host__ __device__ __forceinline__ int entry(int cut) const {
+    const int e = (cut - A - o + 1) & ~1;
+    return e < len ? e : len;
+  }
+};
+
+// The pieces of one (row, tile).
+struct PieceList {
+  int j0, pieces, per_slab, tile;
+  // Slot of piece o's partial result.  An interval holds at most one piece
+  // that continues a row (slot 0) and one that begins a row which goes on
+  // after it (slot 1).
+  __host__ __device__ __forceinline__ int slot(int o, const AttnShares& s) const {
+    const int J = j0 + o, x = J / per_slab, i = J - x * per_slab;
+    const int in_slab = i <= s.s_main
+                            ? i * s.n + tile
+                            : s.n * (s.s_main + 1) + (int)share_next_left(s, tile) - 1;
+    return 2 * (x * s.slots_per_slab + in_slab) + (o == 0 ? 1 : 0);
+  }
+};
+
+// Entries of a row of `len` entries that query tile t can see (the line's w).
+__host__ __device__ __forceinline__ int share_visible(int len, int cached_len, int C, int t, int query_tile, int page) {
+  const int q_end = (t + 1) * query_tile < C ? (t + 1) * query_tile : C;
+  const int unseen = (cached_len + C - 1) / page - (cached_len + q_end - 1) / page;
+  return len - unseen > 1 ? len - unseen : 1;
+}
+
+// Expected share of a row's cached blocks that its table lists (the paper's
+// executed density after both unions is 0.30): only the choice between
+// launches depends on it, never a result's validity.
+constexpr double kListedShare = 0.3;
+// Fewest expected pages per CU for a balanced launch, where other launches leave
+// CUs idle and where uniform splits fill the GPU evenly.
+constexpr double kBalancedMinPages = 4.0, kBalancedMinPagesEven = 32.0;
+constexpr int kMaxUniformSplits = 16;   // of the automatic choice
+// Where the query tiles alone fill the GPU: the largest part of the pages that
+// the causal triangle may take off the first tiles (the CUs of an XCD then
+// differ by about as much).
+constexpr double kBalancedMaxTriangle = 0.18;
+
+// The shares of a launch over `groups` table rows per sequence and n query
+// tiles, or .on = false where another launch is better.
+inline AttnShares attn_shares(int batch, int groups, int C, int n, int query_tile, int head_dim,
+                              int page, const int* cached_len, bool dense) {
+  AttnShares s;
+  const long long R = (long long)batch * groups;
+  if (R > kSharesMaxRows || n >= kAttnCusPerXcd) return s;
+  double line = 0;   // expected entries of all rows
+  bool equal = true;
+  for (int b = 0; b < batch; ++b) {
+    const int nc = cached_len[b] / page, nkb = (cached_len[b] + C - 1) / page + 1;
+    line += groups * (dense ? nkb : nkb - nc + kListedShare * nc);
+    equal = equal && cached_len[b] == cached_len[0];
+  }
+  const int cus = kAttnXcds * kAttnCusPerXcd;
+  const double pages = line * n / cus;   // per CU
+  if (pages < kBalancedMinPages) return s;
+  // rows of (about) one length whose tiles fill the GPU by uniform splits
+  if (equal && cus % (R * n) == 0 && cus / (R * n) <= kMaxUniformSplits &&
+      (dense || pages < kBalancedMinPagesEven))
+    return s;
+  if (R * n >= cus &&
+      R * (n - 1) * (query_tile / (double)page) / 2 > kBalancedMaxTriangle * line)
+    return s;
+  s.on = true;
+  // one tile: its rows packed, so that a tile's rows end with the last query
+  s.query_tile = n == 1 ? C : query_tile;
+  // a piece costs about 12 us, 8 pages of 1.6 us (D = 128); short shares lose
+  // more by rounding to it than the pieces cost
+  const int most = head_dim == 64 ? 6 : 8;
+  const double o = pages / (head_dim == 64 ? 8 : 3);
+  s.overhead = o < 4 ? 4 : o > most ? most : (int)o;
+  s.n = n;
+  s.s_main = kAttnCusPerXcd / n;
+  s.left = kAttnCusPerXcd - n * s.s_main;
+  s.slots_per_slab = n * s.s_main + (s.left > 0 ? n + s.left : 0);
+  return s;
+}
+
 // V page layouts of the pool (ca_problem.v_layout).
 constexpr int kVTokenMajor = 0;   // [P, page, D], like the K pages
 constexpr int kVTransposed = 1;   // [P, D, page]
@@ -82,7 +297,12 @@ struct AttnLaunch {
   // carry equal loads (needs B * G % 8 == 0 and attn_xcd_ws_bytes of ws)
   bool xcd_balanced = false;
   int v_layout = kVTokenMajor;
+  AttnShares shares;   // shares.on: balanced launch (attn_shares_ws_bytes of ws)
 };
+// The shares of a balanced launch of these sizes; .on = false where another
+// launch is better.
+AttnShares attn_shares(const Dims& d, int group_size, const int32_t* cached_len_host, bool dense);
+size_t attn_shares_ws_bytes(const Dims& d, int group_size, const AttnShares& s);
 int attn_rows_per_workgroup(int table_mode);             // (head, query) rows per workgroup
 int attn_query_tile(int group_size, int table_mode);     // chunk queries per workgroup
 int attn_base_workgroups(const Dims& d, int group_size, int table_mode);

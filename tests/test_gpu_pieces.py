@@ -69,3 +69,79 @@ def test_trailing_entries_past_one_window(chunk_open):
                                 4, w.sm_scale, num_splits=1, lse=lse)
     _check(w, d, rows, 4, out, lse)
 
+
+# Launches that share their pages equally among the CUs, around the edges of the
+# schedule: one query tile (32 segments per slab) to 31 tiles (one segment and a
+# remainder on one CU), flat shares of a causal triangle, rows of very different
+# lengths, and rows that list few blocks or none.
+SHARES = [
+    # cached, chunk, heads, dim, group, layout, density (None = dense)
+    ((40000,), 37, (32, 8), 64, 4, 0, 0.3),
+    ((40000,), 1, (32, 8), 128, 4, 1, 0.3),
+    ((20000,), 300, (32, 8), 128, 4, 0, 0.4),
+    ((9000,), 700, (32, 8), 64, 4, 1, 0.5),
+    ((7001,), 1451, (32, 8), 128, 4, 0, 0.6),
+    ((5000,), 1984, (16, 4), 64, 4, 1, 0.6),
+    ((9000, 37, 30000), 200, (32, 8), 64, 4, 0, 0.4),
+    ((6000, 12000), 500, (8, 1), 64, 8, 1, 0.5),
+    ((6000,), 700, (16, 8), 128, 2, 0, 0.4),
+    ((30000,), 999, (4, 1), 64, 4, 0, 0.9),
+    ((3000,), 1024, (32, 8), 64, 4, 1, 0.5),
+    ((0,), 2048, (32, 8), 128, 4, 0, None),
+    ((0, 500), 1000, (32, 8), 64, 4, 1, None),
+    ((100, 3000, 0), 777, (16, 4), 128, 4, 0, None),
+    ((9000,), 999, (16, 4), 64, 4, 0, None),
+]
+
+
+@pytest.mark.parametrize("cached,chunk,heads,dim,group,layout,density", SHARES)
+def test_equal_shares_match_oracle(cached, chunk, heads, dim, group, layout, density):
+    w, d = _inputs(cached, chunk, heads, dim)
+    w = synth.configs.replace(w, group_size=group)
+    x = device_inputs(d, layout)
+    p = ca.Problem.from_workload(w, v_layout=layout)
+    q, kv = x["q"], (x["k"], x["v"])
+    rows, ip, ix = _tables(w, 2.0 if density is None else density, 7)
+    tables = (i32_dev(ip), i32_dev(ix))
+    n = ca.attention_workspace_bytes(p, group, 0)
+    lse = torch.empty((w.batch, heads[0], chunk), dtype=torch.float32, device="cuda")
+
+    def run(fill):
+        ws = torch.full((max(n, 16),), fill, dtype=torch.uint8, device="cuda")
+        lse.fill_(float("nan"))
+        out = torch.full_like(q, float("nan"))
+        if density is None:
+            ca.dense_paged_chunk_attention(p, q, kv, x["pt"], w.sm_scale, out=out, lse=lse, ws=ws)
+        else:
+            ca.chunk_attention(p, q, kv, x["pt"], tables, group, w.sm_scale, out=out, lse=lse,
+                               ws=ws)
+            # the same tables through packed pools
+            packed = ca.gather_selected_pages(p, kv, x["pt"], tables, group)
+            out2, _ = ca.packed_chunk_attention(p, q, packed, tables, group, w.sm_scale, ws=ws)
+            assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
+        return out, lse.clone()
+
+    out, l0 = run(0)
+    again, l1 = run(255)     # whatever the workspace held
+    assert torch.equal(out.view(torch.int16), again.view(torch.int16)) and torch.equal(l0, l1)
+    _check(w, d, rows, group, out, l0, per_tile=2, every=1 if w.batch == 1 else 2)
+
+
+@pytest.mark.parametrize("chunk", [100, 1300])
+def test_equal_shares_sparse_rows(chunk):
+    """Tables that leave out chunk blocks, list one block, or list none: every
+    output is written (0 and -inf for a query that sees no key)."""
+    w, d = _inputs((30000, 8000), chunk, (32, 8))
+    x = device_inputs(d)
+    p = ca.Problem.from_workload(w)
+    rows, _, _ = _tables(w, 0.5, 11, chunk_open=False)
+    rows[1], rows[2] = rows[1][:0], rows[2][:1]
+    rows[9], rows[15] = rows[9][-1:], rows[15][:0]
+    ip = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    ix = np.zeros(len(rows) * w.max_kv_blocks, dtype=np.int32)
+    ix[:ip[-1]] = np.concatenate(rows)
+    lse = torch.full((2, 32, chunk), float("nan"), device="cuda")
+    out = torch.full_like(x["q"], float("nan"))
+    ca.chunk_attention(p, x["q"], (x["k"], x["v"]), x["pt"], (i32_dev(ip), i32_dev(ix)), 4,
+                       w.sm_scale, out=out, lse=lse)
+    _check(w, d, rows, 4, out, lse, every=2)

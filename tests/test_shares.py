@@ -1,0 +1,142 @@
+"""The equal shares of a balanced attention launch (csrc/kernels.hpp), compiled for
+the host and checked against a direct count over many sizes: every entry of every
+(row, query tile) lies in exactly one piece, pieces are numbered in entry order,
+no two pieces share a partial-result slot, slots stay inside the workspace, and no
+CU runs much more than its share of the pages."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+
+DRIVER = r"""
+#include "kernels.hpp"
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <random>
+#include <set>
+#include <vector>
+using namespace ca;
+
+static void die(const char* what) { printf("FAIL %s\n", what); exit(1); }
+
+struct Piece { int e0, e1, pieces, slot; };
+
+int main(int argc, char** argv) {
+  std::mt19937 rng(atoi(argv[1]));
+  auto pick = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
+  int used = 0, even = 0, uneven = 0;
+  for (int trial = 0; trial < 3000; ++trial) {
+    const int gs_of[] = {1, 2, 4, 8};
+    const int gs = gs_of[pick(0, 3)], groups = pick(1, 9), batch = pick(1, 7), QT = 256 / gs;
+    const bool dense = pick(0, 1);
+    const int C = pick(0, 3) ? pick(1, QT * 33) : QT * pick(1, 32);
+    const int n = (C + QT - 1) / QT, page = 64;
+    std::vector<int> cl(batch);
+    for (int& v : cl) v = pick(0, 2) ? pick(0, 6000) : pick(0, 131072);
+    const int D = pick(0, 1) ? 64 : 128;
+    const AttnShares s = attn_shares(batch, groups, C, n, QT, D, page, cl.data(), dense);
+    if (!s.on) continue;
+    ++used;
+    (s.left ? uneven : even)++;
+    const int R = batch * groups;
+    if (R > 64 || n > 31 || n * s.s_main > 32) die("range");
+    std::vector<int> len(R);
+    for (int r = 0; r < R; ++r) {
+      const int nkb = (cl[r / groups] + C + page - 1) / page;
+      // given tables may list anything, the chunk's own blocks or not, or nothing
+      len[r] = dense ? nkb : pick(0, 9) ? pick(std::min(nkb, (C + page - 1) / page), nkb) : pick(0, 2);
+      len[r] = std::min(len[r], nkb);
+    }
+    std::vector<std::vector<ShareRow>> rows(n);
+    std::vector<int> T(n);
+    for (int t = 0; t < n; ++t)
+      for (int r = 0; r < R; ++r) {
+        const int w = share_visible(len[r], cl[r / groups], C, t, s.query_tile, page);
+        rows[t].push_back({T[t], w, len[r], s.overhead});
+        T[t] += w + s.overhead;
+      }
+    std::map<std::pair<int, int>, std::map<int, Piece>> pieces;   // (t, r) -> ordinal -> piece
+    std::set<int> slots;
+    std::vector<long long> load(256);
+    for (int x = 0; x < 8; ++x)
+      for (int c = 0; c < 32; ++c) {
+        const bool main_cu = c < n * s.s_main;
+        std::vector<int> tiles;
+        const int e = c - n * s.s_main, m = s.left;
+        if (main_cu) tiles.push_back(c % n);
+        else for (int t = 0; t < n; ++t)
+          if ((t + 1) * m > e * n && t * m < (e + 1) * n) tiles.push_back(t);
+        for (int t : tiles) {
+          const ShareLine l = share_line(s, T[t], t);
+          const unsigned i = main_cu ? c / n : s.s_main + (e * n > t * m ? 1 : 0);
+          if (i >= l.per) continue;
+          const int lo = share_cut(l, x, i), hi = share_cut(l, x, i + 1);
+          if (lo > hi || lo < (int)share_slab(l, x) || hi > (int)share_slab(l, x + 1)) die("interval");
+          for (int r = 0; r < R; ++r) {
+            const ShareRow& row = rows[t][r];
+            if (!row.meets(lo, hi)) continue;
+            Piece p;
+            p.e0 = lo >= row.first() ? row.entry(lo) : 0;
+            p.e1 = hi <= row.last() ? row.entry(hi) : len[r];
+            const int j0 = share_cuts_upto(l, row.first() - 1);
+            const PieceList q = {j0, (int)share_cuts_upto(l, row.last()) - j0 + 1, (int)l.per, t};
+            const int o = (int)(x * l.per + i) - q.j0;
+            if (o < 0 || o >= q.pieces) die("ordinal");
+            p.pieces = q.pieces;
+            p.slot = q.slot(o, s);
+            if (o > 0 && p.e0 % 2 && p.e0 < len[r]) die("odd cut");
+            if (!pieces[{t, r}].insert({o, p}).second) die("piece twice");
+            if (q.pieces > 1) {
+              if (!slots.insert(p.slot).second) die("slot twice");
+              if (p.slot < 0 || p.slot >= 8 * s.slots_per_slab * 2) die("slot range");
+            }
+            load[x * 32 + c] += std::min(p.e1, row.w) - std::min(p.e0, row.w) + s.overhead;
+          }
+        }
+      }
+    for (int t = 0; t < n; ++t)
+      for (int r = 0; r < R; ++r) {
+        auto it = pieces.find({t, r});
+        if (it == pieces.end()) die("row without a piece");
+        int at = 0, k = 0;
+        for (auto& [o, p] : it->second) {
+          if (o != k++) die("ordinals");
+          if (p.e0 != at || p.e1 < p.e0) die("gap");
+          at = p.e1;
+        }
+        if (at != len[r]) die("row end");
+        if (k != it->second.begin()->second.pieces) die("count");
+      }
+    // the CUs' shares differ by the causal triangle (at most the chunk's
+    // blocks per row end), by what a row's cost moves, and by the rounding of
+    // cuts to pairs and row ends
+    double share = 0;
+    for (unsigned v : T) share += v / 256.0;
+    const long long most = *std::max_element(load.begin(), load.end());
+    if (most > 1.05 * share + (C / page + 2) * (R / 8 + 2) + 10 * s.overhead + 2 * (n + 2) + 4)
+      die("share");
+  }
+  printf("OK %d launches, %d even, %d uneven\n", used, even, uneven);
+  return used > 500 && even > 50 && uneven > 50 ? 0 : 2;
+}
+"""
+
+
+@pytest.mark.parametrize("seed", [1, 2])
+def test_shares_partition_every_row(seed, tmp_path):
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
+    (tmp_path / "driver.hip").write_text(DRIVER)
+    exe = tmp_path / "driver"
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-O2", "-Xclang",
+                    "-target-feature", "-Xclang", "-packed-fp32-ops", "-I",
+                    os.path.join(ROOT, "paper_2605_16839_amd", "csrc"), "-o", str(exe),
+                    str(tmp_path / "driver.hip")], check=True)
+    r = subprocess.run([str(exe), str(seed)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
