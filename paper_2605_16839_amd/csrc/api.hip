@@ -509,17 +509,6 @@ ca_status ca_block_scores(const ca_problem* p, const float* q_mean, const float*
                     "scores launch");
 }
 
-// The keys of one selection row live in LDS: raise the dynamic LDS cap for
-// long caches.
-static ca_status select_lds_ready(const ca::Dims& d) {
-  const size_t lds = (size_t)(d.max_nc > 0 ? d.max_nc : 1) * sizeof(uint32_t);
-  if (lds > 48 * 1024) {
-    hipError_t e = ca::raise_select_lds((int)lds);
-    if (e != hipSuccess) return hip_status(e, "raise select LDS limit");
-  }
-  return CA_OK;
-}
-
 ca_status ca_select_blocks(const ca_problem* p, const float* scores, float top_frac,
                            int32_t sink_blocks, int32_t local_blocks, uint64_t* masks,
                            void* stream) {
@@ -532,7 +521,6 @@ ca_status ca_select_blocks(const ca_problem* p, const float* scores, float top_f
     return fail(CA_ERR_SHAPE, "top_frac must be in [0, 1]");
   if (sink_blocks < 0 || local_blocks < 0)
     return fail(CA_ERR_SHAPE, "sink_blocks and local_blocks must be >= 0");
-  if ((s = select_lds_ready(d)) != CA_OK) return s;
   return hip_status(ca::launch_select(d, scores, p->cached_len, top_frac, sink_blocks,
                                       local_blocks, masks, static_cast<hipStream_t>(stream)),
                     "select launch");
@@ -588,7 +576,6 @@ ca_status ca_estimate_tables(const ca_problem* p, const uint16_t* q, const uint1
                 ws == nullptr ? (size_t)0 : ws_bytes);
   if (reinterpret_cast<uintptr_t>(ws) % sizeof(uint64_t) != 0)
     return fail(CA_ERR_WORKSPACE, "workspace must be 8-byte aligned");
-  if ((s = select_lds_ready(d)) != CA_OK) return s;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   uint64_t* words = static_cast<uint64_t*>(ws);
   hipError_t e = ca::launch_pool(d, q, q_mean, k_pool, page_table, p->cached_len,

@@ -5,8 +5,8 @@
 // block union (Sec. 3.1, Sec. 3.2 first paragraph); per-chunk search cost is
 // first-order under chunked prefill (Sec. 2.1), so every stage here is a
 // single streaming pass: pooling is HBM-bound, scores are a small fp32
-// contraction on the matrix cores, selection is an in-LDS radix select per
-// mask row.
+// contraction on the matrix cores, selection finds the k-th score of a mask row
+// in one workgroup, keys in registers.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -205,32 +205,63 @@ __global__ __launch_bounds__(256) void scores_kernel(const float* __restrict__ q
 }
 
 // ---------------------------------------------------------------------------
-// Selection: one workgroup (4 waves) per mask row (b, h, i).
-// Scores become order-preserving uint32 keys (-0.0 folded onto +0.0); a
-// 4-pass, 8-bit radix select finds the k-th largest key T and how many keys
-// equal to T still have to be taken; those are the ones with the smallest
-// block index (ranked by a ballot/prefix count).  Words of the mask are then
-// emitted directly from wave ballots: wave v of a 256-block slab owns word
-// slab/64 + v.
+// Selection: one workgroup (4 waves) per mask row (b, h, i); thread t holds the
+// keys of blocks t + 256 m, m < M, in registers.  Scores become order-preserving
+// uint32 keys (-0.0 folded onto +0.0).  The k-th key in the order (key
+// descending, block ascending) is found in two steps:
+//   * 256 buckets of equal width between the row's lowest and highest score
+//     (a monotone map, so a higher bucket holds only higher keys).  Their
+//     counts spread over the LDS atomics, where the leading bits of the keys
+//     would put most of a row on a few counters: the radix passes over those
+//     took 25 us for 4096 rows of up to 1562 blocks, most of it in the first
+//     pass's contended atomics;
+//   * the few keys of the bucket that holds the k-th one are ranked directly, a
+//     wave per copy of the work.  A bucket of more than 64 (many equal scores,
+//     or scores far from evenly spread) is searched by radix passes over its
+//     keys and then over the block indices of the keys that tie.
+// A block is then selected by comparing (key, index) with the k-th: the words
+// come straight from wave ballots, wave v of a 256-block slab owning word
+// slab/64 + v, with no ranking of ties and no barrier.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t order_key(float f) {
   uint32_t u = __float_as_uint(f);
   if (u == 0x80000000u) u = 0u;
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
-
-// Block-wide inclusive scan of one int per thread (256 threads).
-__device__ __forceinline__ int block_scan_256(int v, int* wave_tot) {
-  const int w = threadIdx.x >> 6;
-  int incl = wave_inclusive_scan(v);
-  if (lane_id() == 63) wave_tot[w] = incl;
-  __syncthreads();
-  int add = 0;
-  for (int x = 0; x < w; ++x) add += wave_tot[x];
-  __syncthreads();
-  return incl + add;
+__device__ __forceinline__ float key_value(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
+constexpr int kBuckets = 256;
+constexpr int kRanked = kWave;   // largest bucket that is ranked directly
+
+// From counts of 256 digits (in LDS), the digit that holds the r-th element
+// when digits are taken from the highest (DOWN) or the lowest, and the number
+// of elements in the digits before it.  Every wave computes it alone: lane l
+// takes the digits 4l .. 4l+3 of that order.
+template <bool DOWN>
+__device__ __forceinline__ void digit_of(const int* hist, int r, int* digit, int* before,
+                                         int* count) {
+  const int l = lane_id();
+  int c[4];
+  const int4 h = *reinterpret_cast<const int4*>(hist + (DOWN ? 252 - 4 * l : 4 * l));
+  if (DOWN) c[0] = h.w, c[1] = h.z, c[2] = h.y, c[3] = h.x;
+  else c[0] = h.x, c[1] = h.y, c[2] = h.z, c[3] = h.w;
+  const int sum = c[0] + c[1] + c[2] + c[3];
+  const int incl = wave_inclusive_scan(sum);
+  const int lane = __builtin_ctzll(__ballot(incl >= r));   // r <= the total
+  int at = __builtin_amdgcn_readlane(incl - sum, lane), e = 0;
+#pragma unroll
+  for (int x = 0; x < 3; ++x) {
+    const int cx = __builtin_amdgcn_readlane(c[x], lane);
+    if (e == x && at + cx < r) at += cx, e = x + 1;
+  }
+  *before = at;
+  *count = __builtin_amdgcn_readlane(e == 0 ? c[0] : e == 1 ? c[1] : e == 2 ? c[2] : c[3], lane);
+  *digit = DOWN ? 255 - (4 * lane + e) : 4 * lane + e;
+}
+
+template <int M>
 __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ scores,
                                                      const int32_t* __restrict__ cached_len,
                                                      uint64_t* __restrict__ masks, int Hq,
@@ -240,10 +271,11 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ s
                                                      int local_blocks,
                                                      unsigned long long* __restrict__ gwords,
                                                      int group_size) {
-  extern __shared__ uint32_t keys[];
-  __shared__ int hist[256];
-  __shared__ int wave_tot[4];
-  __shared__ int sh_digit, sh_above;
+  __shared__ __attribute__((aligned(16))) int hist[2][kBuckets];
+  __shared__ uint32_t red[2][4];
+  __shared__ uint32_t cand_key[kRanked];
+  __shared__ int cand_idx[kRanked];
+  __shared__ int n_cand;
   const int row = blockIdx.x;
   const int t = threadIdx.x;
   const int wv = t >> 6;
@@ -258,76 +290,133 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ s
     k = k < 0 ? 0 : (k > nc ? nc : k);
   }
   const float* s = scores + (size_t)row * max_kv_blocks;
-  // 8 loads per lane in flight per round (2048 scores)
-  for (int j0 = 0; j0 < nc; j0 += 8 * 256) {
-    float v[8];
+  uint32_t key[M];
+  {
+    float v[M];
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      const int j = j0 + t + 256 * m;
-      v[m] = j < nc ? s[j] : 0.f;
+    for (int m = 0; m < M; ++m) v[m] = t + 256 * m < nc ? s[t + 256 * m] : 0.f;
+#pragma unroll
+    for (int m = 0; m < M; ++m) key[m] = order_key(v[m]);
+  }
+  // the k-th key and its block: everything of (key, index) up to it is taken
+  uint32_t T = 0xffffffffu;   // k = 0: none
+  int Jt = -1;
+  if (k == nc) {              // all (or no candidates)
+    T = 0u;
+    Jt = nc;
+  } else if (k > 0) {
+    uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      if (t + 256 * m < nc) {
+        lo = key[m] < lo ? key[m] : lo;
+        hi = key[m] > hi ? key[m] : hi;
+      }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const uint32_t l2 = __shfl_xor(lo, o, kWave), h2 = __shfl_xor(hi, o, kWave);
+      lo = l2 < lo ? l2 : lo;
+      hi = h2 > hi ? h2 : hi;
     }
+    if (lane_id() == 0) red[0][wv] = lo, red[1][wv] = hi;
+    hist[0][t] = 0;
+    if (t == 0) n_cand = 0;
+    __syncthreads();
+    lo = red[0][0], hi = red[1][0];
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      const int j = j0 + t + 256 * m;
-      if (j < nc) keys[j] = order_key(v[m]);
+    for (int x = 1; x < 4; ++x) {
+      lo = red[0][x] < lo ? red[0][x] : lo;
+      hi = red[1][x] > hi ? red[1][x] : hi;
+    }
+    // buckets of equal width; a range that is not a positive finite number
+    // (equal scores, infinities, NaN) gives one bucket
+    const float base = key_value(lo), range = key_value(hi) - base;
+    const float scale = range > 0.f && range < INFINITY ? 255.99f / range : 0.f;
+    auto bucket = [&](uint32_t x) {
+      const float f = (key_value(x) - base) * scale;   // NaN compares false: bucket 0
+      return f >= 255.f ? 255 : (f > 0.f ? (int)f : 0);
+    };
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      if (t + 256 * m < nc) atomicAdd(&hist[0][bucket(key[m])], 1);
+    __syncthreads();
+    int bkt, before, count;
+    digit_of<true>(hist[0], k, &bkt, &before, &count);
+    int r = k - before;   // the r-th of the bucket is the k-th of the row
+    if (count <= kRanked) {
+#pragma unroll
+      for (int m = 0; m < M; ++m)
+        if (t + 256 * m < nc && bucket(key[m]) == bkt) {
+          const int at = atomicAdd(&n_cand, 1);
+          cand_key[at] = key[m];
+          cand_idx[at] = t + 256 * m;
+        }
+      __syncthreads();
+      const int l = lane_id() < count ? lane_id() : count - 1;
+      const uint32_t ck = cand_key[l];
+      const int ci = cand_idx[l];
+      int rank = 0;   // candidates before this one
+      for (int x = 0; x < count; ++x) {
+        const uint32_t xk = __builtin_amdgcn_readlane(ck, x);
+        const int xi = __builtin_amdgcn_readlane(ci, x);
+        rank += (xk > ck || (xk == ck && xi < ci)) ? 1 : 0;
+      }
+      const int at = __builtin_ctzll(__ballot(rank == r - 1));
+      T = __builtin_amdgcn_readlane(ck, at);
+      Jt = __builtin_amdgcn_readlane(ci, at);
+    } else {
+      // radix passes over the bucket's keys, from the top digit, then over the
+      // indices of the keys equal to T, upwards.  Pass p counts in hist[p % 2]
+      // and clears the other one for the next.
+      uint32_t prefix = 0u, pmask = 0u;
+      int digit;
+      hist[1][t] = 0;
+      __syncthreads();
+      for (int pass = 1; pass <= 4; ++pass) {
+        const int shift = 32 - 8 * pass;
+        int* const h = hist[pass & 1];
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+          if (t + 256 * m < nc && bucket(key[m]) == bkt && (key[m] & pmask) == prefix)
+            atomicAdd(&h[(key[m] >> shift) & 255u], 1);
+        __syncthreads();
+        hist[(pass + 1) & 1][t] = 0;
+        digit_of<true>(h, r, &digit, &before, &count);
+        prefix |= (uint32_t)digit << shift;
+        pmask |= 0xffu << shift;
+        r -= before;
+        __syncthreads();
+      }
+      T = prefix;
+      int top = 0;
+      for (int pass = 5; pass <= 6; ++pass) {
+        int* const h = hist[pass & 1];
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+          const int j = t + 256 * m;
+          if (j < nc && key[m] == T && (pass == 5 || (j >> 8) == top))
+            atomicAdd(&h[pass == 5 ? j >> 8 : j & 255], 1);
+        }
+        __syncthreads();
+        hist[(pass + 1) & 1][t] = 0;
+        digit_of<false>(h, r, &digit, &before, &count);
+        r -= before;
+        if (pass == 5) top = digit;
+        __syncthreads();
+      }
+      Jt = 256 * top + digit;
     }
   }
-  __syncthreads();
-
-  const bool take_all = (k == nc);
-  uint32_t prefix = 0u, pmask = 0u;
-  int remaining = k;
-  if (k > 0 && !take_all) {
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      hist[t] = 0;
-      __syncthreads();
-      for (int j = t; j < nc; j += 256) {
-        const uint32_t key = keys[j];
-        if ((key & pmask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
-      }
-      __syncthreads();
-      // thread t <-> digit 255 - t: the inclusive scan counts keys with digit >= d
-      const int d = 255 - t;
-      const int c = hist[d];
-      const int incl = block_scan_256(c, wave_tot);
-      const int excl = incl - c;
-      if (excl < remaining && remaining <= incl) {
-        sh_digit = d;
-        sh_above = excl;
-      }
-      __syncthreads();
-      prefix |= (uint32_t)sh_digit << shift;
-      pmask |= 0xffu << shift;
-      remaining -= sh_above;
-      __syncthreads();
-    }
-  }
-  const uint32_t T = prefix;
 
   const int causal_end = causal_block_end(cl, C, i, q_block);
   const int sink_end = sink_blocks < nc ? sink_blocks : nc;
   const int local_begin = nc - local_blocks;
-  int carry = 0;  // keys equal to T already seen, in block order
   uint64_t* mrow = masks + (size_t)row * W;
   // fused path: OR the row straight into the words of its group's table row
   const int h = (row / nqb) % Hq;
   unsigned long long* grow =
       gwords ? gwords + ((size_t)b * (Hq / group_size) + h / group_size) * W : nullptr;
-  for (int base = 0; base < W * 64; base += 256) {
-    const int j = base + t;
-    const bool cached = j < nc;
-    const uint32_t key = cached ? keys[j] : 0u;
-    const bool eq = cached && k > 0 && !take_all && key == T;
-    const uint64_t bal = __ballot(eq);
-    if (lane_id() == 0) wave_tot[wv] = __popcll(bal);
-    __syncthreads();
-    int before = carry, total = 0;
-    for (int x = 0; x < 4; ++x) {
-      if (x < wv) before += wave_tot[x];
-      total += wave_tot[x];
-    }
-    const int rank = before + lanes_below(bal);
-    const bool sel = cached && (take_all || (k > 0 && (key > T || (eq && rank < remaining))));
+  auto emit = [&](int j, bool sel) {
     const bool forced = j < nkb && ((j < sink_end) || (j >= local_begin && j < nc) ||
                                     (j >= nc && j < causal_end));
     const uint64_t word = __ballot(sel || forced);
@@ -336,9 +425,13 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ s
       if (grow == nullptr) mrow[widx] = word;
       else if (word) atomicOr(grow + widx, (unsigned long long)word);
     }
-    carry += total;
-    __syncthreads();
+  };
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const int j = t + 256 * m;
+    if (256 * m < W * 64) emit(j, j < nc && (key[m] > T || (key[m] == T && j <= Jt)));
   }
+  for (int base = 256 * M; base < W * 64; base += 256) emit(base + t, false);   // past the cache
 }
 
 // ---------------------------------------------------------------------------
@@ -447,24 +540,24 @@ hipError_t launch_scores(const Dims& d, const float* q_mean, const float* k_mean
   return hipGetLastError();
 }
 
-hipError_t raise_select_lds(int bytes) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-}
-
 hipError_t launch_select(const Dims& d, const float* scores, const int32_t* cached_len,
                          float top_frac, int sink_blocks, int local_blocks, uint64_t* masks,
                          hipStream_t st, uint64_t* group_words, int group_size) {
   dim3 grid(d.B * d.Hq * d.nqb);
-  const size_t lds = (size_t)(d.max_nc > 0 ? d.max_nc : 1) * sizeof(uint32_t);
-  select_kernel<<<grid, 256, lds, st>>>(scores, cached_len, masks, d.Hq, d.nqb,
-                                        d.max_kv_blocks, d.W, d.C, d.q_block, top_frac,
-                                        sink_blocks, local_blocks,
-                                        reinterpret_cast<unsigned long long*>(group_words),
-                                        group_size);
+  auto* gw = reinterpret_cast<unsigned long long*>(group_words);
+  // the keys of the longest row, 256 M of them, in registers
+  auto launch = [&](auto kernel) {
+    kernel<<<grid, 256, 0, st>>>(scores, cached_len, masks, d.Hq, d.nqb, d.max_kv_blocks, d.W,
+                                 d.C, d.q_block, top_frac, sink_blocks, local_blocks, gw,
+                                 group_size);
+  };
+  if (d.max_nc <= 256) launch(select_kernel<1>);
+  else if (d.max_nc <= 1024) launch(select_kernel<4>);
+  else if (d.max_nc <= 2048) launch(select_kernel<8>);
+  else if (d.max_nc <= 4096) launch(select_kernel<16>);
+  else launch(select_kernel<kMaxKvBlocks / 256>);
   return hipGetLastError();
 }
-
 
 hipError_t launch_threshold_select(const Dims& d, const float* scores, const int32_t* cached_len,
                                    float margin, int sink_blocks, int local_blocks,

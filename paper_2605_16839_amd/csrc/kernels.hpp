@@ -32,7 +32,6 @@ hipError_t launch_scores(const Dims& d, const float* q_mean, const float* k_mean
 hipError_t launch_select(const Dims& d, const float* scores, const int32_t* cached_len,
                          float top_frac, int sink_blocks, int local_blocks, uint64_t* masks,
                          hipStream_t st, uint64_t* group_words = nullptr, int group_size = 1);
-hipError_t raise_select_lds(int bytes);
 hipError_t launch_threshold_select(const Dims& d, const float* scores, const int32_t* cached_len,
                                    float margin, int sink_blocks, int local_blocks,
                                    uint64_t* masks, hipStream_t st);

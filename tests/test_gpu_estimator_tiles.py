@@ -1,0 +1,53 @@
+"""Block scores and top-k selection at the edges of their kernels: tile remainders,
+register-held key counts, and score distributions that take each search path."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_16839_amd as ca
+from _helpers import u64_host
+
+pytestmark = pytest.mark.gpu
+
+# keys per thread change after 256, 1024, 2048 and 4096 blocks
+SIZES = [1, 2, 255, 256, 257, 1024, 1025, 2048, 2049, 4097, 9000]
+
+
+def _scores(kind, rng, shape):
+    n = shape[-1]
+    s = rng.standard_normal(shape).astype(np.float32)
+    if kind == "equal":            # one bucket, every key tied
+        s[...] = 1.25
+    elif kind == "outlier":        # one far score: the rest in one bucket
+        s[..., rng.integers(n)] = 1e20
+    elif kind == "clusters":       # buckets of many nearly equal keys
+        s = (np.round(s) + 1e-4 * s).astype(np.float32)
+    elif kind == "huge":           # the range overflows float32
+        s = np.where(s > 0, 3e38, -3e38).astype(np.float32)
+        s[..., ::7] = 0.0
+    elif kind == "tiny":           # denormal range
+        s = (s * np.float32(1e-41)).astype(np.float32)
+    elif kind == "infinite":       # a few infinities of both signs
+        s[..., ::11] = np.inf
+        s[..., 3::13] = -np.inf
+    return s
+
+
+@pytest.mark.parametrize("kind", ["normal", "equal", "outlier", "clusters", "huge", "tiny",
+                                  "infinite"])
+@pytest.mark.parametrize("nc", SIZES)
+def test_select_is_exact(kind, nc):
+    rng = np.random.default_rng(nc)
+    Hq, C, qb = 2, 192, 128
+    maxkb = nc + C // 64
+    p = ca.Problem(1, Hq, 1, 64, qb, C, maxkb, [64 * nc])
+    scores = np.full((1, Hq, 2, maxkb), np.nan, dtype=np.float32)
+    s = _scores(kind, rng, (Hq, 2, nc))
+    scores[0, :, :, :nc] = s
+    for top in sorted({0.0, 0.4 / nc, 1.0 / nc, 0.05, 0.37, 1.0 - 1.0 / nc, 1.0}):
+        ref = oracle.masks_from_scores([s], [64 * nc], C, 64, qb, p.words,
+                                       oracle.EstimatorParams(top, 1, 4))
+        got = ca.select_blocks(p, torch.from_numpy(scores).cuda(), top)
+        assert np.array_equal(u64_host(got), ref), top
+
