@@ -147,55 +147,81 @@ __global__ __launch_bounds__(256) void pool_kernel(const PoolArgs a) {
 // Scores: for one (b, kvh), the ratio*nQB pooled query rows are contiguous in
 // q_mean and the matching score rows are contiguous too.  One wave computes a
 // 32-row x 32-block tile with fp32 matrix instructions (v_mfma_f32_32x32x2_f32,
-// fp32 products and sums), its operands loaded straight into registers: lane
-// l holds row / block l % 32 and, for k-step (t, e), element
-// d = 8t + 4(l / 32) + e of both operands (the contraction over d may take
-// the d in any order as long as both operands share it), so each lane loads
-// its two rows as D/8 float4 pairs.  Four waves per workgroup.
+// fp32 products and sums); a workgroup's four waves cover 32 WR rows x 32 WJ
+// blocks and share their operands through LDS.  Lane l holds row / block l % 32
+// and, for k-step (t, e), element d = 8t + 4(l / 32) + e of both operands (the
+// contraction over d may take the d in any order as long as both operands share
+// it).  Loaded straight into registers, those operands were 32-byte pieces of
+// 32 rows per load, and each wave read both of its own: 9 us at 64 rows x 2016
+// blocks x 8 heads and 29 us at 128 rows x 3354 blocks x 8, where the reads
+// through L2 (440 MB) set the time.  Here a wave loads whole rows, 1 KB per
+// instruction, all before the first is needed.  LDS rows are padded by 16 bytes:
+// the 16 lanes of a read then touch 16 different 16-byte bank slots.
 // ---------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-template <int D>
+template <int D, int WR>
 __global__ __launch_bounds__(256) void scores_kernel(const float* __restrict__ q_mean,
                                                      const float* __restrict__ k_mean,
                                                      const int32_t* __restrict__ cached_len,
                                                      float* __restrict__ scores, int Hq, int Hkv,
-                                                     int nqb, int max_kv_blocks, int n_jt) {
-  constexpr int NT = D / 8;
+                                                     int nqb, int max_kv_blocks, int n_rg) {
+  constexpr int NT = D / 8, WJ = 4 / WR, LD = D + 4, CPR = D / 4;
+  constexpr int QR = 32 * WR, KR = 32 * WJ;              // rows of each operand
+  constexpr int QL = QR * CPR / 256, KL = KR * CPR / 256;   // float4 per thread
+  __shared__ __attribute__((aligned(16))) float qs[QR * LD];
+  __shared__ __attribute__((aligned(16))) float ks[KR * LD];
   const int bk = blockIdx.y;
   const int b = bk / Hkv, kvh = bk % Hkv;
   const int ratio = Hq / Hkv;
   const int nrows = ratio * nqb;
   const int nc = cached_len[b] / kPage;
-  const int l = threadIdx.x & 63;
-  const int tile = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int n_rt = (nrows + 31) / 32;
-  const int rt = tile % n_rt, jt = tile / n_rt;
-  const int r0 = rt * 32, j0 = jt * 32;
-  if (jt >= n_jt || j0 >= nc) return;   // whole wave
+  const int r_wg = (blockIdx.x % n_rg) * QR, j_wg = (blockIdx.x / n_rg) * KR;
+  if (j_wg >= nc) return;   // whole workgroup
   const size_t row_base = ((size_t)b * Hq + (size_t)kvh * ratio) * nqb;
-  const int i = l & 31, h = l >> 5;
-  const bool q_ok = r0 + i < nrows, k_ok = j0 + i < nc;
-  const float* qrow = q_mean + (row_base + (q_ok ? r0 + i : 0)) * D + 4 * h;
-  const float* krow = k_mean + ((size_t)bk * max_kv_blocks + (k_ok ? j0 + i : 0)) * D + 4 * h;
-  float4 qa[NT], kb[NT];
+  const int t = threadIdx.x;
+  // rows past the end repeat the last one; their results are not stored
+  float4 qv[QL], kv[KL];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    qa[t] = q_ok ? *reinterpret_cast<const float4*>(qrow + 8 * t) : make_float4(0.f, 0.f, 0.f, 0.f);
-    kb[t] = k_ok ? *reinterpret_cast<const float4*>(krow + 8 * t) : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int m = 0; m < KL; ++m) {
+    const int x = m * 256 + t, j = j_wg + x / CPR;
+    kv[m] = reinterpret_cast<const float4*>(
+        k_mean + ((size_t)bk * max_kv_blocks + (j < nc ? j : nc - 1)) * D)[x % CPR];
   }
+#pragma unroll
+  for (int m = 0; m < QL; ++m) {
+    const int x = m * 256 + t, r = r_wg + x / CPR;
+    qv[m] = reinterpret_cast<const float4*>(
+        q_mean + (row_base + (r < nrows ? r : nrows - 1)) * D)[x % CPR];
+  }
+#pragma unroll
+  for (int m = 0; m < KL; ++m) {
+    const int x = m * 256 + t;
+    *reinterpret_cast<float4*>(ks + (x / CPR) * LD + 4 * (x % CPR)) = kv[m];
+  }
+#pragma unroll
+  for (int m = 0; m < QL; ++m) {
+    const int x = m * 256 + t;
+    *reinterpret_cast<float4*>(qs + (x / CPR) * LD + 4 * (x % CPR)) = qv[m];
+  }
+  __syncthreads();
+  const int l = t & 63, wv = t >> 6, i = l & 31, h = l >> 5;
+  const int r0 = r_wg + 32 * (wv % WR), j = j_wg + 32 * (wv / WR) + i;
+  const float* qrow = qs + (32 * (wv % WR) + i) * LD + 4 * h;
+  const float* krow = ks + (32 * (wv / WR) + i) * LD + 4 * h;
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qa[t].x, kb[t].x, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qa[t].y, kb[t].y, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qa[t].z, kb[t].z, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qa[t].w, kb[t].w, acc, 0, 0, 0);
+  for (int x = 0; x < NT; ++x) {
+    const float4 qa = *reinterpret_cast<const float4*>(qrow + 8 * x);
+    const float4 kb = *reinterpret_cast<const float4*>(krow + 8 * x);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qa.x, kb.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qa.y, kb.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qa.z, kb.z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qa.w, kb.w, acc, 0, 0, 0);
   }
   // result v of lane l: row 8(v/4) + 4(l/32) + v%4 of the tile, block l % 32
-  const int j = j0 + i;
   if (j >= nc) return;
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
@@ -528,15 +554,17 @@ hipError_t launch_scores(const Dims& d, const float* q_mean, const float* k_mean
                          const int32_t* cached_len, float* scores, hipStream_t st) {
   if (d.max_nc <= 0) return hipSuccess;
   const int nrows = (d.Hq / d.Hkv) * d.nqb;
-  const int n_jt = (d.max_nc + 31) / 32;
-  const int tiles = ((nrows + 31) / 32) * n_jt;
-  dim3 grid((tiles + 3) / 4, d.B * d.Hkv);
-  if (d.D == 128)
-    scores_kernel<128><<<grid, 256, 0, st>>>(q_mean, k_mean, cached_len, scores, d.Hq, d.Hkv,
-                                             d.nqb, d.max_kv_blocks, n_jt);
-  else
-    scores_kernel<64><<<grid, 256, 0, st>>>(q_mean, k_mean, cached_len, scores, d.Hq, d.Hkv,
-                                            d.nqb, d.max_kv_blocks, n_jt);
+  // two row tiles per workgroup where there are two (half the block rows read
+  // per score), else one
+  const int wr = nrows > 32 ? 2 : 1, wj = 4 / wr;
+  const int n_rg = (nrows + 32 * wr - 1) / (32 * wr);
+  dim3 grid(n_rg * ((d.max_nc + 32 * wj - 1) / (32 * wj)), d.B * d.Hkv);
+  auto launch = [&](auto kernel) {
+    kernel<<<grid, 256, 0, st>>>(q_mean, k_mean, cached_len, scores, d.Hq, d.Hkv, d.nqb,
+                                 d.max_kv_blocks, n_rg);
+  };
+  if (d.D == 128) wr == 2 ? launch(scores_kernel<128, 2>) : launch(scores_kernel<128, 1>);
+  else wr == 2 ? launch(scores_kernel<64, 2>) : launch(scores_kernel<64, 1>);
   return hipGetLastError();
 }
 

@@ -51,3 +51,25 @@ def test_select_is_exact(kind, nc):
         got = ca.select_blocks(p, torch.from_numpy(scores).cuda(), top)
         assert np.array_equal(u64_host(got), ref), top
 
+
+@pytest.mark.parametrize("heads,chunk,qb,dim", [
+    ((1, 1), 64, 64, 64), ((4, 1), 128, 128, 128), ((31, 1), 64, 64, 128), ((8, 2), 500, 64, 64),
+    ((33, 1), 64, 64, 128), ((16, 2), 1024, 128, 128), ((13, 1), 320, 64, 64)])
+@pytest.mark.parametrize("cached", [(64 * 31, 100), (64 * 64, 64 * 65), (64 * 129, 0)])
+def test_scores_at_tile_edges(heads, chunk, qb, dim, cached):
+    """Row tiles of 32 (one or two per workgroup) and block tiles of 32, each with
+    one row or block too few or too many; fp32 sums of dim products of values of
+    about 1: an error of 1e-5 is 80 units in the last place of such a sum."""
+    rng = np.random.default_rng(heads[0])
+    maxkb = max((c + chunk + 63) // 64 for c in cached)
+    p = ca.Problem(len(cached), *heads, dim, qb, chunk, maxkb, list(cached))
+    q = rng.standard_normal((len(cached), heads[0], p.n_qblocks, dim)).astype(np.float32)
+    k = rng.standard_normal((len(cached), heads[1], maxkb, dim)).astype(np.float32)
+    got = ca.block_scores(p, torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda()).cpu().numpy()
+    ratio = heads[0] // heads[1]
+    for b, c in enumerate(cached):
+        nc = c // 64
+        ref = np.einsum("hid,hjd->hij", q[b].astype(np.float64),
+                        np.repeat(k[b], ratio, axis=0)[:, :nc].astype(np.float64))
+        assert np.abs(got[b, :, :, :nc] - ref).max(initial=0.0) <= 1e-5 * np.sqrt(dim)
+        assert np.isnan(got[b, :, :, nc:]).all()      # nothing else is written
