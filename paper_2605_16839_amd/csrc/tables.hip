@@ -2,15 +2,16 @@
 // compaction of the union bitmask into CSR kv_indptr / kv_indices
 // (Sec. 3.2 displayed equations; App. B.2 for the CSR pair).
 //
-// Two launches, both integer-only and deterministic:
+// One launch for few rows (tables_kernel), else two, all integer-only and
+// deterministic:
 //   union_kernel   one workgroup per table row r = b*G + g: OR the
 //                  group_size*nQB mask rows of the group word by word in LDS
 //                  (ds_or_b64), clip to nKB_b, store the row's union words and
 //                  its popcount;
 //   compact_kernel one workgroup per row: row offset = sum of the counts of
-//                  earlier rows (no atomics), then 256-block slabs are
-//                  compacted with wave ballots + a 4-wave prefix in LDS, which
-//                  writes the set block ids in ascending order.
+//                  earlier rows (no atomics), one scan of the words'
+//                  popcounts, then every wave writes the set block ids of
+//                  words of its own, in ascending order.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -72,27 +73,39 @@ __global__ __launch_bounds__(256) void union_kernel(const uint64_t* __restrict__
   if (t == 0) counts[r] = red[0] + red[1] + red[2] + red[3];
 }
 
-// Writes the set bits of one row's words, ascending, from row_start on.
-__device__ void compact_row(const uint64_t* __restrict__ gw, int row_start,
-                            int32_t* __restrict__ kv_indices, int W, int* wave_tot) {
-  const int t = threadIdx.x;
-  const int wv = t >> 6;
-  int carry = 0;
-  for (int base = 0; base < W * 64; base += 256) {
-    const int j = base + t;
-    const int w = j >> 6;
-    const bool bit = (w < W) && ((gw[w] >> (j & 63)) & 1ull);
-    const uint64_t bal = __ballot(bit);
-    if (lane_id() == 0) wave_tot[wv] = __popcll(bal);
-    __syncthreads();
-    int before = carry, total = 0;
-    for (int x = 0; x < 4; ++x) {
-      if (x < wv) before += wave_tot[x];
-      total += wave_tot[x];
-    }
-    if (bit) kv_indices[row_start + before + lanes_below(bal)] = j;
-    carry += total;
-    __syncthreads();
+// Writes the set bits of one row's words, ascending, from row_start on.  The
+// words' offsets come from one scan (a word per thread and round); then every
+// wave writes words of its own, 64 bits by 64 lanes, with no further barrier.
+// (256-block slabs with two barriers each took 4.7 us for 32 rows of 2016
+// blocks, launch included.)
+template <int THREADS, typename Words>
+__device__ void compact_row(const Words* gw, int row_start, int32_t* __restrict__ kv_indices,
+                            int W) {
+  __shared__ unsigned long long words[kMaxWords];
+  __shared__ int offset[kMaxWords];
+  __shared__ int tot[4];
+  const int t = threadIdx.x, wv = t >> 6;
+  static_assert(kMaxWords == 256 && THREADS >= 256, "one word per thread, four waves");
+  if (t < kMaxWords) {
+    const unsigned long long v = t < W ? gw[t] : 0ull;
+    const int n = __popcll(v), incl = wave_inclusive_scan(n);
+    if (lane_id() == 63) tot[wv] = incl;
+    words[t] = v;
+    offset[t] = incl - n;
+  }
+  __syncthreads();
+  int before[4], sum = row_start;   // start of each 64-word quarter
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    before[x] = sum;
+    sum += tot[x];
+  }
+#pragma unroll 4
+  for (int w = wv; w < W; w += THREADS / kWave) {
+    const unsigned long long word = words[w];
+    const int q = w >> 6;
+    const int at = offset[w] + (q == 0 ? before[0] : q == 1 ? before[1] : q == 2 ? before[2] : before[3]);
+    if ((word >> lane_id()) & 1ull) kv_indices[at + lanes_below(word)] = 64 * w + lane_id();
   }
 }
 
@@ -101,7 +114,6 @@ __global__ __launch_bounds__(256) void compact_kernel(const uint64_t* __restrict
                                                       int32_t* __restrict__ kv_indptr,
                                                       int32_t* __restrict__ kv_indices, int W) {
   __shared__ int red[4];
-  __shared__ int wave_tot[4];
   const int r = blockIdx.x;
   const int t = threadIdx.x;
   int part = 0;
@@ -114,7 +126,7 @@ __global__ __launch_bounds__(256) void compact_kernel(const uint64_t* __restrict
     if (r == 0) kv_indptr[0] = 0;
     kv_indptr[r + 1] = row_start + counts[r];
   }
-  compact_row(gwords + (size_t)r * W, row_start, kv_indices, W, wave_tot);
+  compact_row<256>(gwords + (size_t)r * W, row_start, kv_indices, W);
 }
 
 // Same, with the counts taken from the words themselves: row r starts after
@@ -125,14 +137,20 @@ __global__ __launch_bounds__(256) void compact_words_kernel(const uint64_t* __re
                                                             int32_t* __restrict__ kv_indices,
                                                             int W) {
   __shared__ int red[8];
-  __shared__ int wave_tot[4];
   const int r = blockIdx.x;
   const int t = threadIdx.x;
   int before = 0, own = 0;
-  for (int x = t; x < (r + 1) * W; x += 256) {
-    const int c = __popcll(gwords[x]);
-    if (x < r * W) before += c;
-    else own += c;
+  // 8 loads per lane in flight per round
+  for (int x0 = t; x0 < (r + 1) * W; x0 += 8 * 256) {
+    uint64_t v[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) v[m] = x0 + 256 * m < (r + 1) * W ? gwords[x0 + 256 * m] : 0ull;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const int c = __popcll(v[m]);
+      if (x0 + 256 * m < r * W) before += c;
+      else own += c;
+    }
   }
   before = wave_sum(before);
   own = wave_sum(own);
@@ -146,7 +164,81 @@ __global__ __launch_bounds__(256) void compact_words_kernel(const uint64_t* __re
     if (r == 0) kv_indptr[0] = 0;
     kv_indptr[r + 1] = row_start + red[4] + red[5] + red[6] + red[7];
   }
-  compact_row(gwords + (size_t)r * W, row_start, kv_indices, W, wave_tot);
+  compact_row<256>(gwords + (size_t)r * W, row_start, kv_indices, W);
+}
+
+// Union and compaction of few rows in one launch: workgroup r forms the union
+// words of rows 0 .. r, a wave per row, from the masks themselves, keeps the
+// counts of the earlier rows for its offset and the words of its own for
+// compact_row.  The masks of the earlier rows are read again by every later
+// row's workgroup, (R + 1) / 2 times the masks in all: up to kTablesOneLaunchReads
+// bytes the kernel takes as long as the two it replaces (6.4 us for 8 rows of 131
+// KB of masks, 7.2 for 16 of 262 KB) and the call 6.5 us instead of 9.5, where the
+// host's second launch set the time; 32 rows of 524 KB (8.7 MB of reads) took
+// 11.5 us against 9.3.
+constexpr int kTablesOneLaunchRows = 64;
+constexpr size_t kTablesOneLaunchReads = 4 << 20;
+constexpr int kTablesThreads = 1024;
+
+// OR over `rows` mask rows of W words: word w of the result in lane w % 64 of
+// round w / 64 (Wp = the power of two from W up, at most 64; 64 / Wp rows are
+// read at once).
+__device__ __forceinline__ unsigned long long or_rows(const uint64_t* __restrict__ src, int rows,
+                                                      int W, int Wp, int w0) {
+  const int l = lane_id(), w = w0 + (l & (Wp - 1)), step = kWave / Wp;
+  unsigned long long v = 0ull;
+  for (int row0 = l / Wp; row0 < rows; row0 += 16 * step) {   // 16 loads in flight
+    unsigned long long x[16];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      const int row = row0 + m * step;
+      x[m] = row < rows && w < W ? src[(size_t)row * W + w] : 0ull;
+    }
+#pragma unroll
+    for (int m = 0; m < 16; ++m) v |= x[m];
+  }
+  for (int o = Wp; o < kWave; o <<= 1) {
+    const unsigned lo = __shfl_xor((unsigned)v, o, kWave);
+    const unsigned hi = __shfl_xor((unsigned)(v >> 32), o, kWave);
+    v |= ((unsigned long long)hi << 32) | lo;
+  }
+  return v;
+}
+
+__global__ __launch_bounds__(kTablesThreads) void tables_kernel(
+    const uint64_t* __restrict__ masks, const int32_t* __restrict__ cached_len,
+    int32_t* __restrict__ kv_indptr, int32_t* __restrict__ kv_indices, int Hq, int nqb, int W,
+    int group_size, int G, int C) {
+  __shared__ unsigned long long own[kMaxWords];
+  __shared__ int counts[kTablesOneLaunchRows];
+  const int r = blockIdx.x, t = threadIdx.x, wv = t >> 6, l = t & 63;
+  const int rows = group_size * nqb;
+  int Wp = 1;
+  while (Wp < W && Wp < kWave) Wp <<= 1;
+  for (int x = wv; x <= r; x += kTablesThreads / kWave) {
+    const int b = x / G, g = x - b * G;
+    const int nkb = blocks_for(cached_len[b] + C);
+    const uint64_t* src = masks + ((size_t)b * Hq + (size_t)g * group_size) * nqb * W;
+    int cnt = 0;
+    for (int w0 = 0; w0 < W; w0 += kWave) {
+      unsigned long long v = or_rows(src, rows, W, Wp, w0);
+      const int w = w0 + l, lo = 64 * w;   // lanes past the words hold copies: not counted
+      if (l >= Wp || lo >= nkb) v = 0ull;
+      else if (nkb - lo < 64) v &= ~0ull >> (64 - (nkb - lo));
+      cnt += __popcll(v);
+      if (x == r && w < W && l < Wp) own[w] = v;
+    }
+    cnt = wave_sum(cnt);
+    if (l == 0) counts[x] = cnt;
+  }
+  __syncthreads();
+  int row_start = 0;
+  for (int x = 0; x < r; ++x) row_start += counts[x];
+  if (t == 0) {
+    if (r == 0) kv_indptr[0] = 0;
+    kv_indptr[r + 1] = row_start + counts[r];
+  }
+  compact_row<kTablesThreads>(own, row_start, kv_indices, W);
 }
 
 hipError_t launch_compact_words(const Dims& d, int rows, const uint64_t* words,
@@ -234,6 +326,12 @@ hipError_t launch_tables(const Dims& d, const uint64_t* masks, const int32_t* ca
                          hipStream_t st) {
   const int G = d.Hq / group_size;
   const int R = d.B * G;
+  const size_t mask_bytes = (size_t)d.B * d.Hq * d.nqb * d.W * sizeof(uint64_t);
+  if (R <= kTablesOneLaunchRows && mask_bytes * (R + 1) / 2 <= kTablesOneLaunchReads) {
+    tables_kernel<<<R, kTablesThreads, 0, st>>>(masks, cached_len, kv_indptr, kv_indices, d.Hq,
+                                                d.nqb, d.W, group_size, G, d.C);
+    return hipGetLastError();
+  }
   uint64_t* gwords = static_cast<uint64_t*>(ws);
   int32_t* counts = reinterpret_cast<int32_t*>(gwords + (size_t)R * d.W);
   union_kernel<<<R, 256, 0, st>>>(masks, cached_len, gwords, counts, d.Hq, d.nqb, d.W,
