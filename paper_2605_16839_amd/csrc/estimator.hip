@@ -7,6 +7,8 @@
 // single streaming pass: pooling is HBM-bound, scores are a small fp32
 // contraction on the matrix cores, selection finds the k-th score of a mask row
 // in one workgroup, keys in registers.
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -465,6 +467,11 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ s
 // mask row keeps every cached block with s_j >= s_max + margin (the sum in
 // fp32), plus the same sink, local and chunk-causal bits as select_kernel.
 // ---------------------------------------------------------------------------
+// Thread t holds the scores of blocks t + 256 m, m < M, in registers: one
+// memory latency, where a loop over the row for the maximum and another for the
+// comparison waited for one per 256 blocks (5.2 us for 256 rows of 1562 blocks,
+// launch included).
+template <int M>
 __global__ __launch_bounds__(256) void threshold_select_kernel(
     const float* __restrict__ scores, const int32_t* __restrict__ cached_len,
     uint64_t* __restrict__ masks, int Hq, int nqb, int max_kv_blocks, int W, int C,
@@ -479,8 +486,11 @@ __global__ __launch_bounds__(256) void threshold_select_kernel(
   const int nc = cl / kPage;
   const int nkb = blocks_for(cl + C);
   const float* s = scores + (size_t)row * max_kv_blocks;
-  float mx = -INFINITY;
-  for (int j = t; j < nc; j += 256) mx = fmaxf(mx, s[j]);
+  float v[M], mx = -INFINITY;
+#pragma unroll
+  for (int m = 0; m < M; ++m) v[m] = t + 256 * m < nc ? s[t + 256 * m] : -INFINITY;
+#pragma unroll
+  for (int m = 0; m < M; ++m) mx = fmaxf(mx, v[m]);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, kWave));
   if (lane_id() == 0) red[wv] = mx;
@@ -491,15 +501,19 @@ __global__ __launch_bounds__(256) void threshold_select_kernel(
   const int sink_end = sink_blocks < nc ? sink_blocks : nc;
   const int local_begin = nc - local_blocks;
   uint64_t* mrow = masks + (size_t)row * W;
-  for (int base = 0; base < W * 64; base += 256) {
-    const int j = base + t;
-    const bool sel = j < nc && s[j] >= thr;
+  auto emit = [&](int j, bool sel) {
     const bool forced = j < nkb && ((j < sink_end) || (j >= local_begin && j < nc) ||
                                     (j >= nc && j < causal_end));
     const uint64_t word = __ballot(sel || forced);
     const int widx = j >> 6;
     if (lane_id() == 0 && widx < W) mrow[widx] = word;
+  };
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const int j = t + 256 * m;
+    if (256 * m < W * 64) emit(j, j < nc && v[m] >= thr);
   }
+  for (int base = 256 * M; base < W * 64; base += 256) emit(base + t, false);   // past the cache
 }
 
 // ---------------------------------------------------------------------------
@@ -568,22 +582,26 @@ hipError_t launch_scores(const Dims& d, const float* q_mean, const float* k_mean
   return hipGetLastError();
 }
 
+// Calls f(integral_constant M): a row of up to max_nc blocks, M per thread.
+template <typename F>
+static void with_keys_per_thread(int max_nc, F f) {
+  if (max_nc <= 256) f(std::integral_constant<int, 1>{});
+  else if (max_nc <= 1024) f(std::integral_constant<int, 4>{});
+  else if (max_nc <= 2048) f(std::integral_constant<int, 8>{});
+  else if (max_nc <= 4096) f(std::integral_constant<int, 16>{});
+  else f(std::integral_constant<int, kMaxKvBlocks / 256>{});
+}
+
 hipError_t launch_select(const Dims& d, const float* scores, const int32_t* cached_len,
                          float top_frac, int sink_blocks, int local_blocks, uint64_t* masks,
                          hipStream_t st, uint64_t* group_words, int group_size) {
   dim3 grid(d.B * d.Hq * d.nqb);
   auto* gw = reinterpret_cast<unsigned long long*>(group_words);
-  // the keys of the longest row, 256 M of them, in registers
-  auto launch = [&](auto kernel) {
-    kernel<<<grid, 256, 0, st>>>(scores, cached_len, masks, d.Hq, d.nqb, d.max_kv_blocks, d.W,
-                                 d.C, d.q_block, top_frac, sink_blocks, local_blocks, gw,
-                                 group_size);
-  };
-  if (d.max_nc <= 256) launch(select_kernel<1>);
-  else if (d.max_nc <= 1024) launch(select_kernel<4>);
-  else if (d.max_nc <= 2048) launch(select_kernel<8>);
-  else if (d.max_nc <= 4096) launch(select_kernel<16>);
-  else launch(select_kernel<kMaxKvBlocks / 256>);
+  with_keys_per_thread(d.max_nc, [&](auto M) {
+    select_kernel<M.value><<<grid, 256, 0, st>>>(scores, cached_len, masks, d.Hq, d.nqb,
+                                                 d.max_kv_blocks, d.W, d.C, d.q_block, top_frac,
+                                                 sink_blocks, local_blocks, gw, group_size);
+  });
   return hipGetLastError();
 }
 
@@ -591,9 +609,11 @@ hipError_t launch_threshold_select(const Dims& d, const float* scores, const int
                                    float margin, int sink_blocks, int local_blocks,
                                    uint64_t* masks, hipStream_t st) {
   dim3 grid(d.B * d.Hq * d.nqb);
-  threshold_select_kernel<<<grid, 256, 0, st>>>(scores, cached_len, masks, d.Hq, d.nqb,
-                                                d.max_kv_blocks, d.W, d.C, d.q_block,
-                                                margin, sink_blocks, local_blocks);
+  with_keys_per_thread(d.max_nc, [&](auto M) {
+    threshold_select_kernel<M.value><<<grid, 256, 0, st>>>(scores, cached_len, masks, d.Hq, d.nqb,
+                                                           d.max_kv_blocks, d.W, d.C, d.q_block,
+                                                           margin, sink_blocks, local_blocks);
+  });
   return hipGetLastError();
 }
 
