@@ -471,8 +471,8 @@ ca_status ca_pool_k_blocks(const ca_problem* p, const uint16_t* k_pool,
     return fail(CA_ERR_NULL, "k_pool, page_table and k_mean are required");
   if ((s = need_aligned16("k_pool and k_mean", k_pool, k_mean)) != CA_OK) return s;
   if (first_block < 0) return fail(CA_ERR_SHAPE, "first_block must be >= 0");
-  return hip_status(ca::launch_pool_k(d, k_pool, page_table, p->cached_len, first_block,
-                                      k_mean, static_cast<hipStream_t>(stream)),
+  return hip_status(ca::launch_pool_k(d, k_pool, page_table, p->cached_len,
+                                      p->cached_len_host, first_block, k_mean, static_cast<hipStream_t>(stream)),
                     "pool_k launch");
 }
 
@@ -490,8 +490,8 @@ static ca_status pool_both(const ca_problem* p, const uint16_t* q, const uint16_
   if ((s = need_aligned16("q, q_mean, k_pool and k_mean", q, q_mean, k_pool, k_mean)) != CA_OK)
     return s;
   if (first_block < 0) return fail(CA_ERR_SHAPE, "first_block must be >= 0");
-  return hip_status(ca::launch_pool(d, q, q_mean, k_pool, page_table, p->cached_len, first_block,
-                                    k_mean, static_cast<hipStream_t>(stream)),
+  return hip_status(ca::launch_pool(d, q, q_mean, k_pool, page_table, p->cached_len,
+                                    p->cached_len_host, first_block, k_mean, static_cast<hipStream_t>(stream)),
                     "pool launch");
 }
 
@@ -579,7 +579,7 @@ ca_status ca_estimate_tables(const ca_problem* p, const uint16_t* q, const uint1
   const hipStream_t st = static_cast<hipStream_t>(stream);
   uint64_t* words = static_cast<uint64_t*>(ws);
   hipError_t e = ca::launch_pool(d, q, q_mean, k_pool, page_table, p->cached_len,
-                                 k_mean_first_block, k_mean, st, words, (int)((size_t)rows * d.W));
+                                 p->cached_len_host, k_mean_first_block, k_mean, st, words, (int)((size_t)rows * d.W));
   if (e == hipSuccess) e = ca::launch_scores(d, q_mean, k_mean, p->cached_len, scores, st);
   if (e == hipSuccess)
     e = ca::launch_select(d, scores, p->cached_len, top_frac, sink_blocks, local_blocks, nullptr,
@@ -683,8 +683,8 @@ ca_status ca_build_block_tables_noalloc(const ca_problem* p, const uint64_t* mas
                 need, (size_t)CA_NOALLOC_SCRATCH_BYTES);
   void* ws = nullptr;
   if ((s = scratch_ptr(&ws)) != CA_OK) return s;
-  // union_kernel writes every word and count that compact_kernel reads, so the
-  // previous call's contents need no clearing
+  // every scratch word and count is written before it is read, so the previous
+  // call's contents need no clearing
   return hip_status(ca::launch_tables(d, masks, p->cached_len, group_size, kv_indptr,
                                       kv_indices, ws, static_cast<hipStream_t>(stream)),
                     "tables launch (allocation-free)");

@@ -63,7 +63,7 @@ __device__ __forceinline__ void pool_rows(const uint16_t* __restrict__ base, siz
 // Exactly N * RPI rows: all N loads are issued before the first add, so a
 // wave keeps N 16-byte loads per lane in flight instead of one (same adds,
 // same order as pool_rows).
-template <int D, int N>
+template <int D, int N, bool NT>
 __device__ __forceinline__ void pool_rows_n(const uint16_t* __restrict__ base, size_t stride,
                                             float* __restrict__ out, float scale) {
   constexpr int CPR = D / 8;
@@ -72,7 +72,11 @@ __device__ __forceinline__ void pool_rows_n(const uint16_t* __restrict__ base, s
   const uint16_t* src = base + (size_t)(l / CPR) * stride + (l % CPR) * 8;
   uint4 v[N];
 #pragma unroll
-  for (int k = 0; k < N; ++k) v[k] = *reinterpret_cast<const uint4*>(src + (size_t)k * RPI * stride);
+  for (int k = 0; k < N; ++k) {
+    const u32x4* const at = reinterpret_cast<const u32x4*>(src + (size_t)k * RPI * stride);
+    const u32x4 x = NT ? __builtin_nontemporal_load(at) : *at;
+    v[k] = make_uint4(x[0], x[1], x[2], x[3]);
+  }
   float acc[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
@@ -103,7 +107,7 @@ struct PoolArgs {
   int Hkv, max_kv_blocks, first_block, k_tiles;   // k_tiles workgroups per (b, kvh)
 };
 
-template <int D>
+template <int D, bool NT>
 __global__ __launch_bounds__(256) void pool_kernel(const PoolArgs a) {
   __shared__ __attribute__((aligned(16))) float part[4][D];
   constexpr int RPI = kWave / (D / 8);
@@ -122,7 +126,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const PoolArgs a) {
     const uint16_t* base =
         a.q + (((size_t)b * a.C + (size_t)i * a.q_block + (size_t)wv * quarter) * a.Hq + h) * D;
     const size_t stride = (size_t)a.Hq * D;
-    if (rows == 8 * RPI) pool_rows_n<D, 8>(base, stride, part[wv], 1.0f);
+    if (rows == 8 * RPI) pool_rows_n<D, 8, false>(base, stride, part[wv], 1.0f);
     else pool_rows<D>(base, stride, rows, part[wv], 1.0f);
     __syncthreads();
     const int t = threadIdx.x;
@@ -141,7 +145,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const PoolArgs a) {
   const int page = a.page_table[(size_t)bk * a.max_kv_blocks + j];
   const uint16_t* base = a.k_pool + (size_t)page * kPage * D;
   float* out = a.k_mean + ((size_t)bk * a.max_kv_blocks + j) * D;
-  if (rows == kPage) pool_rows_n<D, kPage / RPI>(base, D, out, 1.0f / (float)kPage);
+  if (rows == kPage) pool_rows_n<D, kPage / RPI, NT>(base, D, out, 1.0f / (float)kPage);
   else pool_rows<D>(base, D, rows, out, 1.0f / (float)rows);
 }
 
@@ -519,10 +523,13 @@ __global__ __launch_bounds__(256) void threshold_select_kernel(
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+constexpr size_t kLastLevelCacheBytes = 256u << 20;   // MI355X
+
 // q == nullptr: no Q pooling; k_pool == nullptr: no K pooling.
 hipError_t launch_pool(const Dims& d, const uint16_t* q, float* q_mean, const uint16_t* k_pool,
-                       const int32_t* page_table, const int32_t* cached_len, int first_block,
-                       float* k_mean, hipStream_t st, uint64_t* clear_words, int n_clear) {
+                       const int32_t* page_table, const int32_t* cached_len,
+                       const int32_t* cached_len_host, int first_block, float* k_mean,
+                       hipStream_t st, uint64_t* clear_words, int n_clear) {
   PoolArgs a;
   a.q = q;
   a.q_mean = q_mean;
@@ -546,22 +553,34 @@ hipError_t launch_pool(const Dims& d, const uint16_t* q, float* q_mean, const ui
   const long long nwg = (long long)a.n_q_wg + (long long)a.k_tiles * d.B * d.Hkv;
   if (nwg == 0) return hipSuccess;
   if (nwg > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  if (d.D == 128) pool_kernel<128><<<(int)nwg, 256, 0, st>>>(a);
-  else pool_kernel<64><<<(int)nwg, 256, 0, st>>>(a);
+  // K pages that could not stay in the 256 MB last-level cache are streamed
+  // past it (non-temporal): 128K tokens of 8 heads (268 MB, other pools used in
+  // between) 70 -> 63 us for the whole selection, four sequences (474 MB) 138 ->
+  // 127 us; what fits is faster through it when it is read again (57 MB 34
+  // against 36 us).  A step's attention takes as long after either.
+  size_t k_bytes = 0;
+  for (int b = 0; b < d.B && k_pool != nullptr; ++b) {
+    const int blocks = blocks_for(cached_len_host[b] + d.C) - first_block;
+    if (blocks > 0) k_bytes += (size_t)blocks * d.Hkv * kPage * d.D * 2;
+  }
+  const bool nt = k_bytes >= kLastLevelCacheBytes;
+  auto launch = [&](auto kernel) { kernel<<<(int)nwg, 256, 0, st>>>(a); };
+  if (d.D == 128) nt ? launch(pool_kernel<128, true>) : launch(pool_kernel<128, false>);
+  else nt ? launch(pool_kernel<64, true>) : launch(pool_kernel<64, false>);
   return hipGetLastError();
 }
 
 hipError_t launch_pool_q(const Dims& d, const uint16_t* q, float* q_mean, hipStream_t st,
                          uint64_t* clear_words, int n_clear) {
-  return launch_pool(d, q, q_mean, nullptr, nullptr, nullptr, 0, nullptr, st, clear_words,
+  return launch_pool(d, q, q_mean, nullptr, nullptr, nullptr, nullptr, 0, nullptr, st, clear_words,
                      n_clear);
 }
 
 hipError_t launch_pool_k(const Dims& d, const uint16_t* k_pool, const int32_t* page_table,
-                         const int32_t* cached_len, int first_block, float* k_mean,
-                         hipStream_t st) {
-  return launch_pool(d, nullptr, nullptr, k_pool, page_table, cached_len, first_block, k_mean,
-                     st, nullptr, 0);
+                         const int32_t* cached_len, const int32_t* cached_len_host,
+                         int first_block, float* k_mean, hipStream_t st) {
+  return launch_pool(d, nullptr, nullptr, k_pool, page_table, cached_len, cached_len_host,
+                     first_block, k_mean, st, nullptr, 0);
 }
 
 hipError_t launch_scores(const Dims& d, const float* q_mean, const float* k_mean,

@@ -17,14 +17,14 @@ struct Dims {
 // Q-block and K-block pooling in one launch (q or k_pool may be nullptr to
 // skip that part); clear_words[0, n_clear) are zeroed by the same launch.
 hipError_t launch_pool(const Dims& d, const uint16_t* q, float* q_mean, const uint16_t* k_pool,
-                       const int32_t* page_table, const int32_t* cached_len, int first_block,
-                       float* k_mean, hipStream_t st, uint64_t* clear_words = nullptr,
-                       int n_clear = 0);
+                       const int32_t* page_table, const int32_t* cached_len,
+                       const int32_t* cached_len_host, int first_block, float* k_mean,
+                       hipStream_t st, uint64_t* clear_words = nullptr, int n_clear = 0);
 hipError_t launch_pool_q(const Dims& d, const uint16_t* q, float* q_mean, hipStream_t st,
                          uint64_t* clear_words = nullptr, int n_clear = 0);
 hipError_t launch_pool_k(const Dims& d, const uint16_t* k_pool, const int32_t* page_table,
-                         const int32_t* cached_len, int first_block, float* k_mean,
-                         hipStream_t st);
+                         const int32_t* cached_len, const int32_t* cached_len_host,
+                         int first_block, float* k_mean, hipStream_t st);
 hipError_t launch_scores(const Dims& d, const float* q_mean, const float* k_mean,
                          const int32_t* cached_len, float* scores, hipStream_t st);
 // With group_words set, the selected rows are ORed into the (b, group) union
