@@ -267,6 +267,8 @@ ca_status ca_estimate_tables(const ca_problem* p, const uint16_t* q, const uint1
  *    num_splits: 1 = one pass per query tile; > 1 = the table of each row is
  *    cut into that many consecutive pieces whose partial results are merged
  *    by log-sum-exp (needs workspace); 0 = let the library choose:
+ *      - for short rows and chunks with much of a causal triangle: query tiles
+ *        of half the size, two to a CU, no row cut (no workspace is needed);
  *      - when fewer than 32 query tiles share at most 64 table rows and there
  *        is work for every CU (about 4 expected pages each) and the workspace
  *        holds ca_attention_workspace_bytes(p, group_size, 0): one workgroup

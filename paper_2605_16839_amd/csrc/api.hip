@@ -336,18 +336,21 @@ ca_status run_attention(const ca_problem* p, const uint16_t* q, const uint16_t* 
   int splits = num_splits;
   bool xcd = false;
   ca::AttnShares shares;
+  bool half = false;
   if (splits == 0) {
+    half = table_mode != ca::kTablesPerQTile &&
+           ca::attn_half_tiles(d, group_size, p->cached_len_host, dense);
     // equal shares per CU; with too little workspace (or an unaligned one) the
     // launches below, as they take it
-    if (table_mode != ca::kTablesPerQTile && ws != nullptr &&
+    if (!half && table_mode != ca::kTablesPerQTile && ws != nullptr &&
         reinterpret_cast<uintptr_t>(ws) % 16 == 0) {
       shares = ca::attn_shares(d, group_size, p->cached_len_host, dense);
       if (shares.on && ws_bytes < ca::attn_shares_ws_bytes(d, group_size, shares))
         shares.on = false;
     }
-    xcd = !shares.on && xcd_balance_ok(d, p, group_size, table_mode, dense) && ws != nullptr &&
+    xcd = !half && !shares.on && xcd_balance_ok(d, p, group_size, table_mode, dense) && ws != nullptr &&
           ws_bytes >= ca::attn_xcd_ws_bytes(d, group_size);
-    splits = shares.on ? 1 : xcd ? 2 : auto_splits(d, group_size, ws_bytes, ws != nullptr, table_mode);
+    splits = half || shares.on ? 1 : xcd ? 2 : auto_splits(d, group_size, ws_bytes, ws != nullptr, table_mode);
   }
   if (splits > 1) {
     const size_t need = ca::attn_ws_bytes(d, splits);
@@ -372,6 +375,7 @@ ca_status run_attention(const ca_problem* p, const uint16_t* q, const uint16_t* 
   L.splits = splits;
   L.xcd_balanced = xcd;
   L.shares = shares;
+  L.half_tiles = half;
   L.ws = ws;
   L.dense = dense;
   L.table_mode = table_mode;

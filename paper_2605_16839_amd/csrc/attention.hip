@@ -101,6 +101,7 @@ struct AttnArgs {
   int rows_per_unit;   // table rows that read one KV head's pages together
   AttnShares shares;   // balanced launch only (balanced_attention_kernel)
   int4* pieces;        // balanced launch: {j0, pieces, per_slab} of every (row, tile)
+  int pair_tiles;      // half-tile launches: tile order n-1, n-2, .. then 0, 1, ..
 };
 
 constexpr int kXcds = kAttnXcds;   // MI355X: 8 accelerator complex dies, 32 CUs and one L2 each
@@ -1361,6 +1362,12 @@ __device__ __forceinline__ void attend(const AttnArgs& a) {
       }
       sp = rest % a.splits;
       qt = rest / a.splits;
+      if (NW == kWavesQTile && a.pair_tiles) {
+        // the longest tiles first, one per CU, then the shortest beside them:
+        // tiles n-1-k and k share a CU
+        const int first = (a.n_qtiles + 1) / 2;
+        qt = qt < first ? a.n_qtiles - 1 - qt : qt - first;
+      }
     }
     piece(a, threadIdx.x, rowid, qt, sp);
   }
@@ -1667,6 +1674,47 @@ AttnShares attn_shares(const Dims& d, int group_size, const int32_t* cached_len_
                      cached_len_host, dense);
 }
 
+// Half tiles: 128 rows per workgroup, so that two workgroups share a CU and the
+// causal triangle (tile t of a chunk sees t more steps of the cache than tile 0)
+// evens out: tiles n-1-k and k start beside each other, and a CU whose short
+// tile is done gives the long one its whole rate.  No row is cut and no merge
+// follows, which is most of what short rows cost.  Against that, each page is
+// copied to LDS for half the rows, so that longer rows lose (3% at 128K).
+// In us at D = 128, before -> half tiles (one box):
+//   chunk 2048, no cache                56.1 -> 45.0     chunk 64    11.5 ->  8.6
+//   chunk 2048 over 4096, dense        154.4 -> 147.4    chunk 512   26.2 -> 18.6
+//   chunk 2048 over 8192, 0.3 listed   126.0 -> 112.3    chunk 1024  35.7 -> 26.3
+//   chunk 2048 over 16384, dense       450.9 -> 452.5    chunk 1500  50.0 -> 39.9
+//   chunk 500 over 4000, dense          50.5 -> 71.6 (71 pages alone on a CU
+//                                       against four pieces: not chosen)
+// The rule.  Where whole tiles fill the GPU: a triangle of 9% of the pages or
+// more.  Else the times that fit the measured ones: a start of 11 us and 1.0 us
+// per page of the longest row, or 1.1 per page and CU; against 22 us for a start
+// and a merge and 1.85 us per page of 256 rows and CU.  D = 64: 0.6 of a page.
+bool attn_half_tiles(const Dims& d, int group_size, const int32_t* cached_len_host, bool dense) {
+  const int qt = attn_query_tile(group_size, kTablesPerGroup);
+  const int qt_half = attn_query_tile(group_size, kTablesPerQTile);
+  if (qt_half < 1 || attn_rows_per_workgroup(kTablesPerQTile) % group_size != 0) return false;
+  const int n = (d.C + qt - 1) / qt, n_half = (d.C + qt_half - 1) / qt_half;
+  const int G = d.Hq / group_size;
+  const double cus = kXcds * kCusPerXcd;
+  // pages a tile does not see, on average over the tiles
+  const double unseen = (n - 1) * (qt / (double)kPage) / 2;
+  const double unseen_half = (n_half - 1) * (qt_half / (double)kPage) / 2;
+  double longest = 0, line = 0, full = 0, half = 0;
+  for (int b = 0; b < d.B; ++b) {
+    const int nc = cached_len_host[b] / kPage, nkb = blocks_for(cached_len_host[b] + d.C);
+    const double len = dense ? nkb : nkb - nc + expected_listed(nc);
+    longest = len > longest ? len : longest;
+    line += G * len;
+    full += G * n * (len - unseen) / cus;
+    half += G * n_half * (len - unseen_half) / cus;
+  }
+  if ((double)d.B * G * n >= cus) return d.B * G * unseen >= 0.09 * line;
+  const double page = d.D == 64 ? 0.6 : 1.0;
+  return 11 + page * (longest > 1.1 * half ? longest : 1.1 * half) < 22 + 1.85 * page * full;
+}
+
 // Workspace of a balanced launch: the partial results and log-sum-exps of two
 // pieces per interval (fp32), then the piece list of every (row, tile).
 static size_t shares_partial_rows(const AttnShares& s) {
@@ -1743,8 +1791,10 @@ hipError_t launch_attention(const Dims& d, const AttnLaunch& L, hipStream_t st) 
   a.max_kv_blocks = d.max_kv_blocks;
   a.group_size = L.group_size;
   a.G = d.Hq / L.group_size;
-  const int qt = attn_query_tile(L.group_size, L.table_mode);
+  const int tile_mode = L.half_tiles ? kTablesPerQTile : L.table_mode;   // rows per workgroup
+  const int qt = attn_query_tile(L.group_size, tile_mode);
   a.n_qtiles = (d.C + qt - 1) / qt;
+  a.pair_tiles = L.half_tiles;
   a.splits = L.splits;
   a.table_mode = L.table_mode;
   a.packed_pages = L.packed_pages;
@@ -1753,7 +1803,7 @@ hipError_t launch_attention(const Dims& d, const AttnLaunch& L, hipStream_t st) 
   a.rows_per_unit = L.table_mode == kTablesPerQTile ? d.Hq / d.Hkv : 1;
   if (L.xcd_balanced)
     a.split_at = reinterpret_cast<int32_t*>(static_cast<char*>(L.ws) + attn_partial_bytes(d, 2));
-  const int nwg = attn_base_workgroups(d, L.group_size, L.table_mode) * L.splits;
+  const int nwg = attn_base_workgroups(d, L.group_size, tile_mode) * L.splits;
   if (L.xcd_balanced) {
     // per-group rows (selected or packed tables): the tiles attn_xcd_ws_bytes counts
     if (L.splits != 2 || L.table_mode == kTablesPerQTile) return hipErrorInvalidValue;
@@ -1761,7 +1811,7 @@ hipError_t launch_attention(const Dims& d, const AttnLaunch& L, hipStream_t st) 
                                                      attn_xcd_counters_at(d, L.group_size));
     a.tag = next_arrival_tag();
   }
-  const bool qtile = L.table_mode == kTablesPerQTile;
+  const bool qtile = tile_mode == kTablesPerQTile;
   a.pieces = nullptr;
   if (L.shares.on) {
     a.shares = L.shares;

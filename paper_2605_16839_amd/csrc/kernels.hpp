@@ -218,10 +218,14 @@ __host__ __device__ __forceinline__ int share_visible(int len, int cached_len, i
   return len - unseen > 1 ? len - unseen : 1;
 }
 
-// Expected share of a row's cached blocks that its table lists (the paper's
-// executed density after both unions is 0.30): only the choice between
-// launches depends on it, never a result's validity.
-constexpr double kListedShare = 0.3;
+// Cached blocks that a row's table is expected to list: the paper's executed
+// density after both unions is 0.30 on long contexts; short ones keep more (the
+// forced blocks and the union of few top blocks per row: nearly all of 16).
+// Only the choice between launches depends on it, never a result's validity.
+inline double expected_listed(int cached_blocks) {
+  const double n = 16 + 0.3 * cached_blocks;
+  return n < cached_blocks ? n : cached_blocks;
+}
 // Fewest expected pages per CU for a balanced launch, where other launches leave
 // CUs idle and where uniform splits fill the GPU evenly.
 constexpr double kBalancedMinPages = 4.0, kBalancedMinPagesEven = 32.0;
@@ -242,7 +246,7 @@ inline AttnShares attn_shares(int batch, int groups, int C, int n, int query_til
   bool equal = true;
   for (int b = 0; b < batch; ++b) {
     const int nc = cached_len[b] / page, nkb = (cached_len[b] + C - 1) / page + 1;
-    line += groups * (dense ? nkb : nkb - nc + kListedShare * nc);
+    line += groups * (dense ? nkb : nkb - nc + expected_listed(nc));
     equal = equal && cached_len[b] == cached_len[0];
   }
   const int cus = kAttnXcds * kAttnCusPerXcd;
@@ -297,10 +301,14 @@ struct AttnLaunch {
   bool xcd_balanced = false;
   int v_layout = kVTokenMajor;
   AttnShares shares;   // shares.on: balanced launch (attn_shares_ws_bytes of ws)
+  bool half_tiles = false;   // 128 rows per workgroup, two workgroups per CU; splits == 1
 };
 // The shares of a balanced launch of these sizes; .on = false where another
 // launch is better.
 AttnShares attn_shares(const Dims& d, int group_size, const int32_t* cached_len_host, bool dense);
+// Whether short rows are better run as tiles of 128 rows, two workgroups to a
+// CU and no row cut (attention.hip).
+bool attn_half_tiles(const Dims& d, int group_size, const int32_t* cached_len_host, bool dense);
 size_t attn_shares_ws_bytes(const Dims& d, int group_size, const AttnShares& s);
 int attn_rows_per_workgroup(int table_mode);             // (head, query) rows per workgroup
 int attn_query_tile(int group_size, int table_mode);     // chunk queries per workgroup

@@ -145,3 +145,49 @@ def test_equal_shares_sparse_rows(chunk):
     ca.chunk_attention(p, x["q"], (x["k"], x["v"]), x["pt"], (i32_dev(ip), i32_dev(ix)), 4,
                        w.sm_scale, out=out, lse=lse)
     _check(w, d, rows, 4, out, lse, every=2)
+
+
+# Half tiles (128 rows per workgroup): one query up to more tiles than fit the GPU
+# at once, partial tiles, group sizes that change the queries per tile, rows that do
+# not spread over the XCDs evenly, unaligned lengths, selected and packed tables.
+HALF = [
+    # cached, chunk, heads, dim, group, layout, density (None = dense)
+    ((0,), 1, (4, 1), 64, 4, 0, None),
+    ((0,), 64, (32, 8), 128, 4, 0, None),
+    ((0,), 97, (32, 8), 128, 4, 1, None),
+    ((37,), 512, (32, 8), 128, 4, 0, None),
+    ((0, 0), 700, (32, 8), 64, 4, 1, None),
+    ((100, 0, 300), 333, (12, 3), 128, 4, 0, None),
+    ((0,), 2048, (32, 8), 64, 4, 0, None),
+    ((0,), 300, (16, 2), 64, 8, 1, None),
+    ((500,), 400, (16, 8), 128, 2, 0, 0.5),
+    ((64,), 129, (8, 8), 64, 1, 0, 0.5),
+    ((3000,), 2048, (32, 8), 64, 4, 0, 0.4),
+    ((700, 2100), 2048, (32, 8), 128, 4, 1, 0.3),
+]
+
+
+@pytest.mark.parametrize("cached,chunk,heads,dim,group,layout,density", HALF)
+def test_half_tiles_match_oracle(cached, chunk, heads, dim, group, layout, density):
+    test_equal_shares_match_oracle(cached, chunk, heads, dim, group, layout, density)
+
+
+def test_half_tiles_sparse_rows():
+    """Rows that leave out chunk blocks or list nothing; no workspace at all."""
+    w, d = _inputs((900,), 600, (32, 8))
+    x = device_inputs(d)
+    p = ca.Problem.from_workload(w)
+    rows, _, _ = _tables(w, 0.5, 13, chunk_open=False)
+    rows[1], rows[2], rows[3] = rows[1][:0], rows[2][:1], rows[3][-1:]
+    ip = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    ix = np.zeros(len(rows) * w.max_kv_blocks, dtype=np.int32)
+    ix[:ip[-1]] = np.concatenate(rows)
+    lse = torch.full((1, 32, 600), float("nan"), device="cuda")
+    out = torch.full_like(x["q"], float("nan"))
+    ip_dev, ix_dev = i32_dev(ip), i32_dev(ix)
+    st = ca.load().ca_chunk_attention(
+        p.ref, x["q"].data_ptr(), x["k"].data_ptr(), x["v"].data_ptr(), x["pt"].data_ptr(),
+        ip_dev.data_ptr(), ix_dev.data_ptr(), 4, w.sm_scale, 0, out.data_ptr(),
+        lse.data_ptr(), None, 0, torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    _check(w, d, rows, 4, out, lse)
