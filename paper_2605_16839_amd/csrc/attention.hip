@@ -488,6 +488,7 @@ struct ShareWalk {
   int t, r_next;        // the tile and the first row not yet run; t < 0: done
   // the current piece
   int row, tile, e0, e1, ordinal;
+  int cached, first, length;   // the row's cached_len, first table entry and entries
   PieceList list;
 
   __device__ __forceinline__ ShareWalk(int bid, const AttnArgs& a)
@@ -505,9 +506,13 @@ struct ShareWalk {
     const int lr = lane < R ? lane : R - 1;
     if (t < 0) return false;
     const int cl = a.cached_len[lr / a.G];
-    int len;
-    if (DENSE) len = blocks_for(cl + a.C);
-    else len = a.kv_indptr[lr + 1] - a.kv_indptr[lr];
+    int len, at = 0;
+    if (DENSE) {
+      len = blocks_for(cl + a.C);
+    } else {
+      at = a.kv_indptr[lr];
+      len = a.kv_indptr[lr + 1] - at;
+    }
     while (t >= 0) {
       const int w = share_visible(len, cl, a.C, t, s.query_tile, kPage);
       const int cost = lane < R ? w + s.overhead : 0;
@@ -528,6 +533,9 @@ struct ShareWalk {
                             __builtin_amdgcn_readlane(w, row),
                             __builtin_amdgcn_readlane(len, row), s.overhead};
         tile = t;
+        cached = __builtin_amdgcn_readlane(cl, row);
+        first = __builtin_amdgcn_readlane(at, row);
+        length = r.len;
         e0 = lo >= r.first() ? r.entry(lo) : 0;
         e1 = hi <= r.last() ? r.entry(hi) : r.len;
         list.j0 = (int)share_cuts_upto(line, r.first() - 1);
@@ -611,7 +619,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a) {
     if (!valid[c]) tq[c] = a.C - 1;    // computes a copy of a real row, never stored
   }
   const int kvh = (g * gs) / (a.Hq / a.Hkv);
-  const int cl = a.cached_len[b];
+  const int cl = BAL ? walk.cached : a.cached_len[b];   // the walk has just read them
   const int nkb = blocks_for(cl + a.C);
   int qpos[NCT];
 #pragma unroll
@@ -622,6 +630,9 @@ __device__ __forceinline__ void attend(const AttnArgs& a) {
   int len, tbase = 0;
   if (DENSE) {
     len = nkb;
+  } else if (BAL) {
+    tbase = walk.first;
+    len = walk.length;
   } else {
     // per-group rows, or one row per (head, query tile) for the block-sparse arm
     const int trow = a.table_mode == kTablesPerQTile ? rowid * a.n_qtiles + qt : rowid;
@@ -1558,46 +1569,47 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
 }
 
 // Merge of the pieces of a balanced launch: lse = log sum_i exp(lse_i),
-// out = sum_i exp(lse_i - lse) o_i, pieces in order.  One wave per fragment of
-// a tile (16 rows x 16 d, as the attention kernel's registers lie): each piece's
-// fragment is one 1 KB load, up to kCombineInFlight pieces in flight.  A tile
-// that one piece ran whole has its output already.
-template <int D>
+// out = sum_i exp(lse_i - lse) o_i.  PAR waves per fragment of a tile (16 rows x
+// 16 d, as the attention kernel's registers lie): wave p takes pieces p, p + PAR,
+// .. in order, each piece's fragment one 1 KB load and up to kCombineInFlight of
+// them in flight, and the waves' sums meet in LDS in order.  PAR = 4 for rows of
+// many pieces: 33 pieces of one tile per row took 11 us in one wave per fragment
+// (five batches one after another).  A tile that one piece ran whole has its
+// output already.
+template <int D, int PAR>
 __global__ __launch_bounds__(256) void combine_pieces_kernel(const AttnArgs a) {
   constexpr int NDT = D / 16, FRAGS = NDT * kColTiles, NW = kWavesGroup;
   constexpr int ROWS = 16 * kColTiles * NW;
-  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);   // (row, tile, wave, fragment)
+  const int w = threadIdx.x >> 6, p = w % PAR;
+  const int unit = blockIdx.x * (4 / PAR) + w / PAR;   // (row, tile, wave, fragment)
   const int f = unit % FRAGS, wv = (unit / FRAGS) % NW, tile = unit / (FRAGS * NW);
   const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
   const int n = a.n_qtiles, r = tile / n, t = tile - r * n;
   const int4 d = a.pieces[tile];
-  if (d.y == 1) return;
   const PieceList list = {d.x, d.y, d.z, t};
   // the fragment's rows, as in the attention kernel
   const int QT = a.shares.query_tile, row = wv * 16 * kColTiles + 16 * (f % kColTiles) + col;
   const int b = r / a.G, head = (r - b * a.G) * a.group_size + row / QT;
   const int tq = t * QT + row % QT;
   const bool valid = row < a.group_size * QT && tq < a.C;
-  if (__ballot(valid) == 0) return;
-  auto slot = [&](int i) {
-    return (size_t)list.slot(i, a.shares);
-  };
+  // with PAR = 4 the workgroup has one fragment: it leaves as a whole
+  if (list.pieces == 1 || __ballot(valid) == 0) return;
   float mx = -INFINITY, wsum = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int i0 = 0; i0 < list.pieces; i0 += kCombineInFlight) {
+  for (int i0 = p; i0 < list.pieces; i0 += PAR * kCombineInFlight) {
     // a batch of pieces; a batch with a higher maximum rescales what came before
     float l[kCombineInFlight], m_new = mx;
     float4 v[kCombineInFlight];
 #pragma unroll
     for (int k = 0; k < kCombineInFlight; ++k) {
-      if (i0 + k < list.pieces) {
-        const size_t sl = slot(i0 + k);
+      if (i0 + k * PAR < list.pieces) {
+        const size_t sl = list.slot(i0 + k * PAR, a.shares);
         l[k] = a.part_lse[sl * ROWS + row];
         v[k] = reinterpret_cast<const float4*>(a.part_o)[(sl * NW + wv) * (FRAGS * 64) + f * 64 + lane];
       }
     }
 #pragma unroll
     for (int k = 0; k < kCombineInFlight; ++k)
-      if (i0 + k < list.pieces) m_new = fmaxf(m_new, l[k]);
+      if (i0 + k * PAR < list.pieces) m_new = fmaxf(m_new, l[k]);
     if (m_new == -INFINITY) continue;
     const float keep = mx == -INFINITY ? 0.f : expf(mx - m_new);
     mx = m_new;
@@ -1606,13 +1618,33 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(const AttnArgs a) {
     for (int e = 0; e < 4; ++e) acc[e] *= keep;
 #pragma unroll
     for (int k = 0; k < kCombineInFlight; ++k) {
-      if (i0 + k >= list.pieces || l[k] == -INFINITY) continue;
+      if (i0 + k * PAR >= list.pieces || l[k] == -INFINITY) continue;
       const float wgt = expf(l[k] - mx);
       wsum += wgt;
       acc[0] = fmaf(wgt, v[k].x, acc[0]);
       acc[1] = fmaf(wgt, v[k].y, acc[1]);
       acc[2] = fmaf(wgt, v[k].z, acc[2]);
       acc[3] = fmaf(wgt, v[k].w, acc[3]);
+    }
+  }
+  if constexpr (PAR > 1) {
+    __shared__ float s_mx[PAR][kWave], s_sum[PAR][kWave];
+    __shared__ float4 s_acc[PAR][kWave];
+    s_mx[p][lane] = mx;
+    s_sum[p][lane] = wsum;
+    s_acc[p][lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    __syncthreads();
+    if (p != 0) return;
+#pragma unroll
+    for (int x = 1; x < PAR; ++x) mx = fmaxf(mx, s_mx[x][lane]);
+    wsum = acc[0] = acc[1] = acc[2] = acc[3] = 0.f;
+#pragma unroll
+    for (int x = 0; x < PAR; ++x) {
+      const float m = s_mx[x][lane], wgt = m == -INFINITY ? 0.f : expf(m - mx);
+      const float4 v = s_acc[x][lane];
+      wsum = fmaf(wgt, s_sum[x][lane], wsum);
+      acc[0] = fmaf(wgt, v.x, acc[0]), acc[1] = fmaf(wgt, v.y, acc[1]);
+      acc[2] = fmaf(wgt, v.z, acc[2]), acc[3] = fmaf(wgt, v.w, acc[3]);
     }
   }
   if (!valid) return;
@@ -1759,7 +1791,11 @@ static void launch_balanced(const AttnArgs& a, bool dense, hipStream_t st) {
   if (dense) balanced_attention_kernel<D, NW, kColTiles, true, VL><<<grid, 64 * NW, 0, st>>>(a);
   else balanced_attention_kernel<D, NW, kColTiles, false, VL><<<grid, 64 * NW, 0, st>>>(a);
   const int units = a.B * a.G * a.n_qtiles * NW * (D / 16) * kColTiles;
-  combine_pieces_kernel<D><<<units / 4, 256, 0, st>>>(a);
+  // a row has about 8 s_main / (rows of the line) pieces; four waves to a
+  // fragment pay from about 16 (37-token tail at 64K: 60.8 -> 56.5 us), and cost
+  // more than they save at 5 (512 tokens at 32K: 90 -> 97 us)
+  if (kXcds * a.shares.s_main >= 16 * a.B * a.G) combine_pieces_kernel<D, 4><<<units, 256, 0, st>>>(a);
+  else combine_pieces_kernel<D, 1><<<units / 4, 256, 0, st>>>(a);
 }
 
 template <int D, int NW>
