@@ -253,7 +253,7 @@ __global__ __launch_bounds__(256) void scores_kernel(const float* __restrict__ q
 //     keys and then over the block indices of the keys that tie.
 // A block is then selected by comparing (key, index) with the k-th: the words
 // come straight from wave ballots, wave v of a 256-block slab owning word
-// slab/64 + v, with no ranking of ties and no barrier.
+// slab/64 + v, with no ranking of ties and one barrier.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t order_key(float f) {
   uint32_t u = __float_as_uint(f);
@@ -308,6 +308,7 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ s
   __shared__ uint32_t cand_key[kRanked];
   __shared__ int cand_idx[kRanked];
   __shared__ int n_cand;
+  __shared__ unsigned long long words[kMaxKvBlocks / 64];
   const int row = blockIdx.x;
   const int t = threadIdx.x;
   const int wv = t >> 6;
@@ -443,20 +444,11 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ s
   const int causal_end = causal_block_end(cl, C, i, q_block);
   const int sink_end = sink_blocks < nc ? sink_blocks : nc;
   const int local_begin = nc - local_blocks;
-  uint64_t* mrow = masks + (size_t)row * W;
-  // fused path: OR the row straight into the words of its group's table row
-  const int h = (row / nqb) % Hq;
-  unsigned long long* grow =
-      gwords ? gwords + ((size_t)b * (Hq / group_size) + h / group_size) * W : nullptr;
   auto emit = [&](int j, bool sel) {
     const bool forced = j < nkb && ((j < sink_end) || (j >= local_begin && j < nc) ||
                                     (j >= nc && j < causal_end));
     const uint64_t word = __ballot(sel || forced);
-    const int widx = j >> 6;
-    if (lane_id() == 0 && widx < W) {
-      if (grow == nullptr) mrow[widx] = word;
-      else if (word) atomicOr(grow + widx, (unsigned long long)word);
-    }
+    if (lane_id() == 0) words[j >> 6] = word;   // j < 64 * 256
   };
 #pragma unroll
   for (int m = 0; m < M; ++m) {
@@ -464,6 +456,19 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ s
     if (256 * m < W * 64) emit(j, j < nc && (key[m] > T || (key[m] == T && j <= Jt)));
   }
   for (int base = 256 * M; base < W * 64; base += 256) emit(base + t, false);   // past the cache
+  // The row leaves in one run of words.  One word at a time, the fused path's
+  // ORs into the group words (64 rows on the same 32 words at 128K, from every
+  // XCD) queued behind each other: 21.9 us against 11.9 for the masks.
+  __syncthreads();
+  if (t < W) {
+    const unsigned long long word = words[t];
+    if (gwords == nullptr) {
+      masks[(size_t)row * W + t] = word;
+    } else if (word) {   // fused path: straight into the words of the group's table row
+      const int h = (row / nqb) % Hq;
+      atomicOr(gwords + ((size_t)b * (Hq / group_size) + h / group_size) * W + t, word);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
