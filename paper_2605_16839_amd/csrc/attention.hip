@@ -1200,7 +1200,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a) {
     // as the registers lie: fragment (x, c) of a wave is 64 float4, so that a
     // store writes 1 KB in one run and combine_pieces_kernel reads it so (rows
     // of D floats made 16 runs of 64 bytes of it)
-    const size_t slot = walk.list.slot(walk.ordinal, a.shares);
+    const size_t slot = walk.list.slot(walk.ordinal, rowid * a.n_qtiles + qt, a.shares);
     float4* po = reinterpret_cast<float4*>(a.part_o) + (slot * NW + wv) * (NDT * NCT * 64) + lane;
     float* pl = a.part_lse + slot * ROWS + wv * 16 * NCT + col;
 #pragma unroll
@@ -1602,7 +1602,7 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(const AttnArgs a) {
 #pragma unroll
     for (int k = 0; k < kCombineInFlight; ++k) {
       if (i0 + k * PAR < list.pieces) {
-        const size_t sl = list.slot(i0 + k * PAR, a.shares);
+        const size_t sl = list.slot(i0 + k * PAR, tile, a.shares);
         l[k] = a.part_lse[sl * ROWS + row];
         v[k] = reinterpret_cast<const float4*>(a.part_o)[(sl * NW + wv) * (FRAGS * 64) + f * 64 + lane];
       }
@@ -1747,10 +1747,10 @@ bool attn_half_tiles(const Dims& d, int group_size, const int32_t* cached_len_ho
   return 11 + page * (longest > 1.1 * half ? longest : 1.1 * half) < 22 + 1.85 * page * full;
 }
 
-// Workspace of a balanced launch: the partial results and log-sum-exps of two
-// pieces per interval (fp32), then the piece list of every (row, tile).
+// Workspace of a balanced launch: the partial results and log-sum-exps of its
+// slots (fp32), then the piece list of every (row, tile).
 static size_t shares_partial_rows(const AttnShares& s) {
-  return (size_t)kXcds * s.slots_per_slab * 2 * attn_rows_per_workgroup(kTablesPerGroup);
+  return (size_t)s.slots * attn_rows_per_workgroup(kTablesPerGroup);
 }
 
 static size_t shares_lists_at(const Dims& d, const AttnShares& s) {

@@ -96,6 +96,8 @@ struct AttnShares {
   int overhead = 0;        // cost of a piece's start and end, in entries
   int query_tile = 0;      // chunk queries per tile
   int slots_per_slab = 0;  // intervals of one slab over all tiles
+  bool first_by_row = true;   // slots of rows' first pieces: see PieceList
+  int slots = 0;           // partial results a launch can store
 };
 
 // a / b for a quotient below 2^20 (one step of correction on the float one).
@@ -200,14 +202,17 @@ struct ShareRow {
 struct PieceList {
   int j0, pieces, per_slab, tile;
   // Slot of piece o's partial result.  An interval holds at most one piece
-  // that continues a row (slot 0) and one that begins a row which goes on
-  // after it (slot 1).
-  __host__ __device__ __forceinline__ int slot(int o, const AttnShares& s) const {
+  // that continues a row, and one that begins a row which goes on after it; a
+  // row's first piece is also the only one of its (row, tile), whichever is
+  // the smaller number.
+  __host__ __device__ __forceinline__ int slot(int o, int row_tile, const AttnShares& s) const {
+    const int first = kAttnXcds * s.slots_per_slab;
+    if (o == 0 && s.first_by_row) return first + row_tile;
     const int J = j0 + o, x = J / per_slab, i = J - x * per_slab;
     const int in_slab = i <= s.s_main
                             ? i * s.n + tile
                             : s.n * (s.s_main + 1) + (int)share_next_left(s, tile) - 1;
-    return 2 * (x * s.slots_per_slab + in_slab) + (o == 0 ? 1 : 0);
+    return (o == 0 ? first : 0) + x * s.slots_per_slab + in_slab;
   }
 };
 
@@ -271,6 +276,9 @@ inline AttnShares attn_shares(int batch, int groups, int C, int n, int query_til
   s.s_main = kAttnCusPerXcd / n;
   s.left = kAttnCusPerXcd - n * s.s_main;
   s.slots_per_slab = n * s.s_main + (s.left > 0 ? n + s.left : 0);
+  s.first_by_row = R * n < kAttnXcds * s.slots_per_slab;
+  s.slots = kAttnXcds * s.slots_per_slab +
+            (s.first_by_row ? (int)(R * n) : kAttnXcds * s.slots_per_slab);
   return s;
 }
 

@@ -89,12 +89,12 @@ int main(int argc, char** argv) {
             const int o = (int)(x * l.per + i) - q.j0;
             if (o < 0 || o >= q.pieces) die("ordinal");
             p.pieces = q.pieces;
-            p.slot = q.slot(o, s);
+            p.slot = q.slot(o, r * n + t, s);
             if (o > 0 && p.e0 % 2 && p.e0 < len[r]) die("odd cut");
             if (!pieces[{t, r}].insert({o, p}).second) die("piece twice");
             if (q.pieces > 1) {
               if (!slots.insert(p.slot).second) die("slot twice");
-              if (p.slot < 0 || p.slot >= 8 * s.slots_per_slab * 2) die("slot range");
+              if (p.slot < 0 || p.slot >= s.slots) die("slot range");
             }
             load[x * 32 + c] += std::min(p.e1, row.w) - std::min(p.e0, row.w) + s.overhead;
           }
