@@ -263,7 +263,7 @@ ca_status ca_estimate_tables(const ca_problem* p, const uint16_t* q, const uint1
  *        out = softmax(sm_scale * q.k) . v      (bf16 MFMA, fp32 softmax)
  *    Table entries must be ascending and < nKB_b; blocks are read in place
  *    through page_table (no gather).  A query that sees no key gets out = 0,
- *    lse = -inf.
+ *    lse = -inf; one with a score of NaN or +inf gets out = NaN, lse = -inf.
  *    num_splits: 1 = one pass per query tile; > 1 = the table of each row is
  *    cut into that many consecutive pieces whose partial results are merged
  *    by log-sum-exp (needs workspace); 0 = let the library choose:

@@ -1159,9 +1159,13 @@ __device__ __forceinline__ void attend(const AttnArgs& a) {
   size_t qrow_idx[NCT];
 #pragma unroll
   for (int c = 0; c < NCT; ++c) {
+    // a row sum of NaN (a NaN score, or scores that overflow) leaves out = NaN,
+    // as o is NaN too, and lse = -inf; a piece keeps the NaN in its lse, so that
+    // the merges, which drop pieces of -inf, pass it on
     const float l_tot = groups_sum(l_run[c]);
     inv[c] = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    lse_val[c] = l_tot > 0.f ? (m_run[c] + log2f(l_tot)) * kLn2 : -INFINITY;
+    lse_val[c] = l_tot > 0.f ? (m_run[c] + log2f(l_tot)) * kLn2
+                             : (whole || l_tot == 0.f ? -INFINITY : l_tot);
     qrow_idx[c] = ((size_t)b * a.Hq + head[c]) * a.C + tq[c];
   }
   auto store_out = [&](int c, const float (&v)[NDT][4], float scale, float lse_row) {
@@ -1300,7 +1304,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a) {
     // pieces in order (the arithmetic of the merge launch)
     const float lo = a.part_lse[(size_t)(1 - sp) * nrows + row];
     const float l0 = sp == 0 ? lse_val[c] : lo, l1 = sp == 0 ? lo : lse_val[c];
-    const float mx = fmaxf(l0, l1);
+    const float mx = max2(l0, l1);   // NaN where a piece's is
     float wsum = 0.f;
     if (mx != -INFINITY) {
       const float w0 = l0 == -INFINITY ? 0.f : expf(l0 - mx);
@@ -1311,7 +1315,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a) {
         for (int x = 0; x < NDT; ++x)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            acc[x][e] = (w0 > 0.f ? w0 * v0[x][e] : 0.f) + (w1 > 0.f ? w1 * v1[x][e] : 0.f);
+            acc[x][e] = (w0 != 0.f ? w0 * v0[x][e] : 0.f) + (w1 != 0.f ? w1 * v1[x][e] : 0.f);
       };
       if (sp == 0) sum2(mine, other);   // sp is uniform over the workgroup
       else sum2(other, mine);
@@ -1469,7 +1473,8 @@ hipError_t launch_gather(const Dims& d, const uint16_t* k_pool, const uint16_t* 
 }
 
 // Merge of uniform split-KV pieces: lse = log sum_i exp(lse_i),
-// out = sum_i exp(lse_i - lse) o_i, pieces in order.  One 32-lane half-wave
+// out = sum_i exp(lse_i - lse) o_i, pieces in order.  A piece of NaN makes the
+// row NaN (its lse -inf), as in a launch that does not cut the row.  One 32-lane half-wave
 // per (b, h, t) row, 4 floats of d per lane (D = 128) or 2 (D = 64).  (The
 // XCD-balanced split merges its two pieces inside the attention launch.)
 // Up to kCombineInFlight pieces are loaded all at once.
@@ -1506,14 +1511,14 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
     const float l0 = part_lse[row], l1 = part_lse[nrows + row];
     load_part(0, v0);
     load_part(1, v1);
-    mx = fmaxf(l0, l1);
+    mx = max2(l0, l1);
     if (mx != -INFINITY) {
       const float w0 = l0 == -INFINITY ? 0.f : expf(l0 - mx);
       const float w1 = l1 == -INFINITY ? 0.f : expf(l1 - mx);
       wsum = w0 + w1;
 #pragma unroll
       for (int x = 0; x < PER; ++x)
-        acc[x] = (w0 > 0.f ? w0 * v0[x] : 0.f) + (w1 > 0.f ? w1 * v1[x] : 0.f);
+        acc[x] = (w0 != 0.f ? w0 * v0[x] : 0.f) + (w1 != 0.f ? w1 * v1[x] : 0.f);
     }
   } else if (splits <= kCombineInFlight) {
     // every piece's lse and partial loaded before the first is needed (one
@@ -1528,7 +1533,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
     }
 #pragma unroll
     for (int i = 0; i < kCombineInFlight; ++i)
-      if (i < splits) mx = fmaxf(mx, l[i]);
+      if (i < splits) mx = max2(mx, l[i]);
     if (mx != -INFINITY) {
 #pragma unroll
       for (int i = 0; i < kCombineInFlight; ++i) {
@@ -1540,7 +1545,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
       }
     }
   } else {
-    for (int i = 0; i < splits; ++i) mx = fmaxf(mx, part_lse[(size_t)i * nrows + row]);
+    for (int i = 0; i < splits; ++i) mx = max2(mx, part_lse[(size_t)i * nrows + row]);
     if (mx != -INFINITY) {
       for (int i = 0; i < splits; ++i) {
         const float li = part_lse[(size_t)i * nrows + row];
@@ -1609,7 +1614,7 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(const AttnArgs a) {
     }
 #pragma unroll
     for (int k = 0; k < kCombineInFlight; ++k)
-      if (i0 + k * PAR < list.pieces) m_new = fmaxf(m_new, l[k]);
+      if (i0 + k * PAR < list.pieces) m_new = max2(m_new, l[k]);
     if (m_new == -INFINITY) continue;
     const float keep = mx == -INFINITY ? 0.f : expf(mx - m_new);
     mx = m_new;
@@ -1636,7 +1641,7 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(const AttnArgs a) {
     __syncthreads();
     if (p != 0) return;
 #pragma unroll
-    for (int x = 1; x < PAR; ++x) mx = fmaxf(mx, s_mx[x][lane]);
+    for (int x = 1; x < PAR; ++x) mx = max2(mx, s_mx[x][lane]);
     wsum = acc[0] = acc[1] = acc[2] = acc[3] = 0.f;
 #pragma unroll
     for (int x = 0; x < PAR; ++x) {
