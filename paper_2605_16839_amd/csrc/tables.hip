@@ -170,15 +170,37 @@ __global__ __launch_bounds__(256) void compact_words_kernel(const uint64_t* __re
 // Union and compaction of few rows in one launch: workgroup r forms the union
 // words of rows 0 .. r, a wave per row, from the masks themselves, keeps the
 // counts of the earlier rows for its offset and the words of its own for
-// compact_row.  The masks of the earlier rows are read again by every later
-// row's workgroup, (R + 1) / 2 times the masks in all: up to kTablesOneLaunchReads
-// bytes the kernel takes as long as the two it replaces (6.4 us for 8 rows of 131
-// KB of masks, 7.2 for 16 of 262 KB) and the call 6.5 us instead of 9.5, where the
-// host's second launch set the time; 32 rows of 524 KB (8.7 MB of reads) took
-// 11.5 us against 9.3.
-constexpr int kTablesOneLaunchRows = 64;
+// compact_row.  It saves the host's second launch, which sets the time of the
+// two it replaces (8.1-9 us in all).  Two lines bound it:
+//   * the masks of the earlier rows are read again by every later row's
+//     workgroup, (R + 1) / 2 times the masks in all: 32 rows of 524 KB (8.7 MB of
+//     reads) took 11.5 us against 9.3;
+//   * a wave waits for its loads one round after another: table rows of the wave
+//     (R / 16) x 64-word windows x rounds of 16 loads over the mask rows.  Up to 4
+//     rounds 5.6-9.3 us against 8.1-11.7 (128 mask rows of 32 words 6.1 : 8.4, 32
+//     of 128 words 7.3 : 8.6, 16 of 256 words 8.5 : 10.6), with more than 16 table
+//     rows up to 3 (48 rows 7.6-8.2 : 8.5-9.1; 64 rows, 4 rounds, 9.0-9.8 :
+//     8.8-9.2).  Past the line one wave reads for long: 1 row of 256 x 32 words
+//     8.8 : 8.3, of 512 x 32 13.9 : 9.3, of 512 x 256 90 : 46.
 constexpr size_t kTablesOneLaunchReads = 4 << 20;
 constexpr int kTablesThreads = 1024;
+constexpr int kTablesWaves = kTablesThreads / kWave;
+constexpr int kTablesRowsInFlight = 16;   // loads per round of a wave
+constexpr int kTablesOneLaunchRows = 3 * kTablesWaves;
+
+// Rounds of loads that a wave of the last workgroup waits for in turn.
+static int tables_wave_rounds(int rows, int mask_rows, int W) {
+  int Wp = 1;
+  while (Wp < W && Wp < kWave) Wp <<= 1;
+  const int per_round = kTablesRowsInFlight * (kWave / Wp);
+  return ((rows + kTablesWaves - 1) / kTablesWaves) * ((W + kWave - 1) / kWave) *
+         ((mask_rows + per_round - 1) / per_round);
+}
+
+static bool tables_one_launch(int rows, int mask_rows, int W, size_t mask_bytes) {
+  return mask_bytes * (rows + 1) / 2 <= kTablesOneLaunchReads &&
+         tables_wave_rounds(rows, mask_rows, W) <= (rows <= kTablesWaves ? 4 : 3);
+}
 
 // OR over `rows` mask rows of W words: word w of the result in lane w % 64 of
 // round w / 64 (Wp = the power of two from W up, at most 64; 64 / Wp rows are
@@ -187,15 +209,15 @@ __device__ __forceinline__ unsigned long long or_rows(const uint64_t* __restrict
                                                       int W, int Wp, int w0) {
   const int l = lane_id(), w = w0 + (l & (Wp - 1)), step = kWave / Wp;
   unsigned long long v = 0ull;
-  for (int row0 = l / Wp; row0 < rows; row0 += 16 * step) {   // 16 loads in flight
-    unsigned long long x[16];
+  for (int row0 = l / Wp; row0 < rows; row0 += kTablesRowsInFlight * step) {
+    unsigned long long x[kTablesRowsInFlight];
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
+    for (int m = 0; m < kTablesRowsInFlight; ++m) {
       const int row = row0 + m * step;
       x[m] = row < rows && w < W ? src[(size_t)row * W + w] : 0ull;
     }
 #pragma unroll
-    for (int m = 0; m < 16; ++m) v |= x[m];
+    for (int m = 0; m < kTablesRowsInFlight; ++m) v |= x[m];
   }
   for (int o = Wp; o < kWave; o <<= 1) {
     const unsigned lo = __shfl_xor((unsigned)v, o, kWave);
@@ -210,12 +232,12 @@ __global__ __launch_bounds__(kTablesThreads) void tables_kernel(
     int32_t* __restrict__ kv_indptr, int32_t* __restrict__ kv_indices, int Hq, int nqb, int W,
     int group_size, int G, int C) {
   __shared__ unsigned long long own[kMaxWords];
-  __shared__ int counts[kTablesOneLaunchRows];
+  __shared__ int counts[kTablesOneLaunchRows];   // rows whose rounds are at most 3
   const int r = blockIdx.x, t = threadIdx.x, wv = t >> 6, l = t & 63;
   const int rows = group_size * nqb;
   int Wp = 1;
   while (Wp < W && Wp < kWave) Wp <<= 1;
-  for (int x = wv; x <= r; x += kTablesThreads / kWave) {
+  for (int x = wv; x <= r; x += kTablesWaves) {
     const int b = x / G, g = x - b * G;
     const int nkb = blocks_for(cached_len[b] + C);
     const uint64_t* src = masks + ((size_t)b * Hq + (size_t)g * group_size) * nqb * W;
@@ -327,7 +349,7 @@ hipError_t launch_tables(const Dims& d, const uint64_t* masks, const int32_t* ca
   const int G = d.Hq / group_size;
   const int R = d.B * G;
   const size_t mask_bytes = (size_t)d.B * d.Hq * d.nqb * d.W * sizeof(uint64_t);
-  if (R <= kTablesOneLaunchRows && mask_bytes * (R + 1) / 2 <= kTablesOneLaunchReads) {
+  if (tables_one_launch(R, group_size * d.nqb, d.W, mask_bytes)) {
     tables_kernel<<<R, kTablesThreads, 0, st>>>(masks, cached_len, kv_indptr, kv_indices, d.Hq,
                                                 d.nqb, d.W, group_size, G, d.C);
     return hipGetLastError();

@@ -1,5 +1,6 @@
-"""Block tables around the line between one launch and two (64 rows, 4 MiB of mask
-reads) and at the edges of the word layout (one word, 32, 64 and 256 words)."""
+"""Block tables around the line between one launch and two (48 rows, 4 MiB of mask
+reads, four rounds of loads per wave) and at the edges of the word layout (one word,
+32, 64 and 256 words)."""
 import numpy as np
 import pytest
 import torch
@@ -16,7 +17,11 @@ pytestmark = pytest.mark.gpu
     (1, 4, 4, 64),      # 1 row
     (2, 12, 2, 200),    # 12 rows of two heads x 4 Q-blocks
     (8, 8, 1, 64),      # 64 rows
-    (5, 13, 1, 64),     # 65 rows: two launches
+    (5, 13, 1, 64),     # 65 rows
+    (6, 8, 1, 64),      # 48 rows
+    (7, 7, 1, 64),      # 49 rows: two launches
+    (1, 8, 8, 1024),    # 128 mask rows: one launch up to 32 words
+    (2, 4, 4, 1024),    # 64 mask rows: one launch up to 64 words
     (4, 32, 4, 1100),   # up to 4.7 MB of masks
 ])
 def test_tables_match_oracle(blocks, batch, heads, gs, chunk):
