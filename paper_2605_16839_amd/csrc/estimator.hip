@@ -248,9 +248,14 @@ __global__ __launch_bounds__(256) void scores_kernel(const float* __restrict__ q
 //     took 25 us for 4096 rows of up to 1562 blocks, most of it in the first
 //     pass's contended atomics;
 //   * the few keys of the bucket that holds the k-th one are ranked directly, a
-//     wave per copy of the work.  A bucket of more than 64 (many equal scores,
-//     or scores far from evenly spread) is searched by radix passes over its
-//     keys and then over the block indices of the keys that tie.
+//     wave per copy of the work.  A bucket of more than 64 keys (scores far from
+//     evenly spread: an outlier, clusters) is cut into 256 buckets again, between
+//     its own lowest and highest key; from the third time on the buckets are of
+//     equal width in the keys' integer order, whose lowest and highest key always
+//     part, so that the search ends.  Equal keys are told apart by block index.
+//     In us for 512 rows, with radix passes over the bucket's keys instead, and
+//     so: 2016 blocks, one score of 1e4 13.9, 9.4; all equal 27.5, 5.3; 5000
+//     blocks in clusters 34.4, 21.4 (evenly spread scores: 6.8, 6.9).
 // A block is then selected by comparing (key, index) with the k-th: the words
 // come straight from wave ballots, wave v of a 256-block slab owning word
 // slab/64 + v, with no ranking of ties and one barrier.
@@ -267,18 +272,14 @@ __device__ __forceinline__ float key_value(uint32_t k) {
 constexpr int kBuckets = 256;
 constexpr int kRanked = kWave;   // largest bucket that is ranked directly
 
-// From counts of 256 digits (in LDS), the digit that holds the r-th element
-// when digits are taken from the highest (DOWN) or the lowest, and the number
-// of elements in the digits before it.  Every wave computes it alone: lane l
-// takes the digits 4l .. 4l+3 of that order.
-template <bool DOWN>
-__device__ __forceinline__ void digit_of(const int* hist, int r, int* digit, int* before,
-                                         int* count) {
+// From the counts of the buckets (in LDS), the one that holds the r-th element
+// counted from the highest, its count, and the number of elements above it.
+// Every wave computes it alone: lane l takes the buckets 255-4l .. 252-4l.
+__device__ __forceinline__ void bucket_of(const int* counts, int r, int* bkt, int* above,
+                                          int* count) {
   const int l = lane_id();
-  int c[4];
-  const int4 h = *reinterpret_cast<const int4*>(hist + (DOWN ? 252 - 4 * l : 4 * l));
-  if (DOWN) c[0] = h.w, c[1] = h.z, c[2] = h.y, c[3] = h.x;
-  else c[0] = h.x, c[1] = h.y, c[2] = h.z, c[3] = h.w;
+  const int4 h = *reinterpret_cast<const int4*>(counts + 252 - 4 * l);
+  const int c[4] = {h.w, h.z, h.y, h.x};
   const int sum = c[0] + c[1] + c[2] + c[3];
   const int incl = wave_inclusive_scan(sum);
   const int lane = __builtin_ctzll(__ballot(incl >= r));   // r <= the total
@@ -288,9 +289,9 @@ __device__ __forceinline__ void digit_of(const int* hist, int r, int* digit, int
     const int cx = __builtin_amdgcn_readlane(c[x], lane);
     if (e == x && at + cx < r) at += cx, e = x + 1;
   }
-  *before = at;
+  *above = at;
   *count = __builtin_amdgcn_readlane(e == 0 ? c[0] : e == 1 ? c[1] : e == 2 ? c[2] : c[3], lane);
-  *digit = DOWN ? 255 - (4 * lane + e) : 4 * lane + e;
+  *bkt = 255 - (4 * lane + e);
 }
 
 template <int M>
@@ -331,6 +332,12 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ s
 #pragma unroll
     for (int m = 0; m < M; ++m) key[m] = order_key(v[m]);
   }
+  // f(m, j) for the thread's blocks j; rounds past the row's end are skipped whole
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      if ((M < 32 || 256 * m < nc) && t + 256 * m < nc) f(m, t + 256 * m);
+  };
   // the k-th key and its block: everything of (key, index) up to it is taken
   uint32_t T = 0xffffffffu;   // k = 0: none
   int Jt = -1;
@@ -338,52 +345,80 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ s
     T = 0u;
     Jt = nc;
   } else if (k > 0) {
-    uint32_t lo = 0xffffffffu, hi = 0u;
+    // the r-th key of those in [lo, hi] is the k-th of the row
+    uint32_t lo, hi;
+    int r = k;
+    auto extremes = [&](auto in) {   // lowest and highest key of those with in(key)
+      uint32_t l1 = 0xffffffffu, h1 = 0u;
+      each([&](int m, int) {
+        if (in(key[m])) {
+          l1 = key[m] < l1 ? key[m] : l1;
+          h1 = key[m] > h1 ? key[m] : h1;
+        }
+      });
 #pragma unroll
-    for (int m = 0; m < M; ++m)
-      if (t + 256 * m < nc) {
-        lo = key[m] < lo ? key[m] : lo;
-        hi = key[m] > hi ? key[m] : hi;
+      for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t l2 = __shfl_xor(l1, o, kWave), h2 = __shfl_xor(h1, o, kWave);
+        l1 = l2 < l1 ? l2 : l1;
+        h1 = h2 > h1 ? h2 : h1;
       }
+      if (lane_id() == 0) red[0][wv] = l1, red[1][wv] = h1;
+      __syncthreads();
+      lo = red[0][0], hi = red[1][0];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const uint32_t l2 = __shfl_xor(lo, o, kWave), h2 = __shfl_xor(hi, o, kWave);
-      lo = l2 < lo ? l2 : lo;
-      hi = h2 > hi ? h2 : hi;
-    }
-    if (lane_id() == 0) red[0][wv] = lo, red[1][wv] = hi;
-    hist[0][t] = 0;
-    if (t == 0) n_cand = 0;
-    __syncthreads();
-    lo = red[0][0], hi = red[1][0];
-#pragma unroll
-    for (int x = 1; x < 4; ++x) {
-      lo = red[0][x] < lo ? red[0][x] : lo;
-      hi = red[1][x] > hi ? red[1][x] : hi;
-    }
-    // buckets of equal width; a range that is not a positive finite number
-    // (equal scores, infinities, NaN) gives one bucket
-    const float base = key_value(lo), range = key_value(hi) - base;
-    const float scale = range > 0.f && range < INFINITY ? 255.99f / range : 0.f;
-    auto bucket = [&](uint32_t x) {
-      const float f = (key_value(x) - base) * scale;   // NaN compares false: bucket 0
-      return f >= 255.f ? 255 : (f > 0.f ? (int)f : 0);
+      for (int x = 1; x < 4; ++x) {
+        lo = red[0][x] < lo ? red[0][x] : lo;
+        hi = red[1][x] > hi ? red[1][x] : hi;
+      }
     };
-#pragma unroll
-    for (int m = 0; m < M; ++m)
-      if (t + 256 * m < nc) atomicAdd(&hist[0][bucket(key[m])], 1);
-    __syncthreads();
-    int bkt, before, count;
-    digit_of<true>(hist[0], k, &bkt, &before, &count);
-    int r = k - before;   // the r-th of the bucket is the k-th of the row
-    if (count <= kRanked) {
-#pragma unroll
-      for (int m = 0; m < M; ++m)
-        if (t + 256 * m < nc && bucket(key[m]) == bkt) {
+    // One level of the search among the keys from lo to hi (FIRST: all keys), in
+    // buckets of equal width: by value on the first two levels, where the range is
+    // a positive finite number (not so with infinities or NaN: one bucket then),
+    // else by the keys' order.
+    auto cut = [&](auto FIRST, int level) -> bool {
+      constexpr bool kFirst = decltype(FIRST)::value;
+      int* const counts = hist[level & 1];
+      const float base = key_value(lo), range = key_value(hi) - base;
+      const bool finite = range > 0.f && range < INFINITY, by_value = kFirst || (level == 1 && finite);
+      const float scale = kFirst && !finite ? 0.f : 255.99f / (by_value ? range : (float)(hi - lo));
+      const uint32_t from = lo, to = hi;
+      auto bucket = [&](uint32_t x) {
+        const float f = (by_value ? key_value(x) - base : (float)(x - from)) * scale;
+        return f >= 255.f ? 255 : (f > 0.f ? (int)f : 0);   // (NaN compares false: bucket 0)
+      };
+      auto member = [&](uint32_t x) { return kFirst || (x >= from && x <= to); };
+      // 64 atomics on one counter are served one after another: a wave whose
+      // first round falls into one bucket adds the lanes of such a round at once
+      const int b0 = __builtin_amdgcn_readfirstlane(bucket(key[0]));
+      if (__ballot(bucket(key[0]) != b0) != 0) {
+        each([&](int m, int) {
+          if (member(key[m])) atomicAdd(&counts[bucket(key[m])], 1);
+        });
+      } else {
+        each([&](int m, int) {
+          const int b = member(key[m]) ? bucket(key[m]) : -1;
+          const uint64_t same = __ballot(b == b0);
+          if (b >= 0 && b != b0) atomicAdd(&counts[b], 1);
+          else if (b == b0 && lane_id() == __builtin_ctzll(same)) atomicAdd(&counts[b0], __popcll(same));
+        });
+      }
+      __syncthreads();
+      int bkt, above, count;
+      bucket_of(counts, r, &bkt, &above, &count);
+      r -= above;
+      if (count > kRanked) {
+        // the next level's counters: their last reader was a level ago
+        hist[(level + 1) & 1][t] = 0;
+        extremes([&](uint32_t x) { return member(x) && bucket(x) == bkt; });
+        return false;
+      }
+      each([&](int m, int j) {
+        if (member(key[m]) && bucket(key[m]) == bkt) {
           const int at = atomicAdd(&n_cand, 1);
           cand_key[at] = key[m];
-          cand_idx[at] = t + 256 * m;
+          cand_idx[at] = j;
         }
+      });
       __syncthreads();
       const int l = lane_id() < count ? lane_id() : count - 1;
       const uint32_t ck = cand_key[l];
@@ -397,47 +432,41 @@ __global__ __launch_bounds__(256) void select_kernel(const float* __restrict__ s
       const int at = __builtin_ctzll(__ballot(rank == r - 1));
       T = __builtin_amdgcn_readlane(ck, at);
       Jt = __builtin_amdgcn_readlane(ci, at);
-    } else {
-      // radix passes over the bucket's keys, from the top digit, then over the
-      // indices of the keys equal to T, upwards.  Pass p counts in hist[p % 2]
-      // and clears the other one for the next.
-      uint32_t prefix = 0u, pmask = 0u;
-      int digit;
-      hist[1][t] = 0;
-      __syncthreads();
-      for (int pass = 1; pass <= 4; ++pass) {
-        const int shift = 32 - 8 * pass;
-        int* const h = hist[pass & 1];
+      return true;
+    };
+    hist[0][t] = 0;
+    if (t == 0) n_cand = 0;
+    extremes([](uint32_t) { return true; });
+    if (lo != hi && !cut(std::true_type{}, 0))
+      for (int level = 1; lo != hi && !cut(std::false_type{}, level);) ++level;
+    if (Jt < 0) {
+      // more than 64 equal keys (or a row of one value): the r-th of them by
+      // block.  Rounds of 256 blocks first, then a wave's 64, then the bit.
+      T = lo;
 #pragma unroll
-        for (int m = 0; m < M; ++m)
-          if (t + 256 * m < nc && bucket(key[m]) == bkt && (key[m] & pmask) == prefix)
-            atomicAdd(&h[(key[m] >> shift) & 255u], 1);
-        __syncthreads();
-        hist[(pass + 1) & 1][t] = 0;
-        digit_of<true>(h, r, &digit, &before, &count);
-        prefix |= (uint32_t)digit << shift;
-        pmask |= 0xffu << shift;
-        r -= before;
-        __syncthreads();
-      }
-      T = prefix;
-      int top = 0;
-      for (int pass = 5; pass <= 6; ++pass) {
-        int* const h = hist[pass & 1];
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-          const int j = t + 256 * m;
-          if (j < nc && key[m] == T && (pass == 5 || (j >> 8) == top))
-            atomicAdd(&h[pass == 5 ? j >> 8 : j & 255], 1);
+      for (int m = 0; m < M; ++m)
+        if (256 * m < nc) {
+          const uint64_t word = __ballot(t + 256 * m < nc && key[m] == T);
+          if (lane_id() == 0) words[4 * m + wv] = word;
         }
-        __syncthreads();
-        hist[(pass + 1) & 1][t] = 0;
-        digit_of<false>(h, r, &digit, &before, &count);
-        r -= before;
-        if (pass == 5) top = digit;
-        __syncthreads();
+      __syncthreads();
+      // lane l: words 4l .. 4l+3 (those of round l)
+      int c[4] = {0, 0, 0, 0};
+      if (256 * lane_id() < nc)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) c[x] = __popcll(words[4 * lane_id() + x]);
+      const int sum = c[0] + c[1] + c[2] + c[3], incl = wave_inclusive_scan(sum);
+      const int lane = __builtin_ctzll(__ballot(incl >= r));
+      int rest = r - __builtin_amdgcn_readlane(incl - sum, lane), x = 0;
+#pragma unroll
+      for (int y = 0; y < 3; ++y) {
+        const int cy = __builtin_amdgcn_readlane(c[y], lane);
+        if (x == y && rest > cy) rest -= cy, x = y + 1;
       }
-      Jt = 256 * top + digit;
+      const unsigned long long word = words[4 * lane + x];
+      const uint64_t hit = __ballot(((word >> lane_id()) & 1ull) && lanes_below(word) == rest - 1);
+      Jt = 64 * (4 * lane + x) + __builtin_ctzll(hit);
+      __syncthreads();   // the words are written anew below
     }
   }
 
@@ -606,13 +635,16 @@ hipError_t launch_scores(const Dims& d, const float* q_mean, const float* k_mean
   return hipGetLastError();
 }
 
-// Calls f(integral_constant M): a row of up to max_nc blocks, M per thread.
+// Calls f(integral_constant M): a row of up to max_nc blocks, M per thread.  The
+// rounds of a longer M are skipped or run empty: 5000 blocks took 18.8 us with 64
+// keys per thread and take 13.7 with 32.
 template <typename F>
 static void with_keys_per_thread(int max_nc, F f) {
   if (max_nc <= 256) f(std::integral_constant<int, 1>{});
   else if (max_nc <= 1024) f(std::integral_constant<int, 4>{});
   else if (max_nc <= 2048) f(std::integral_constant<int, 8>{});
   else if (max_nc <= 4096) f(std::integral_constant<int, 16>{});
+  else if (max_nc <= 8192) f(std::integral_constant<int, 32>{});
   else f(std::integral_constant<int, kMaxKvBlocks / 256>{});
 }
 

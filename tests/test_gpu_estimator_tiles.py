@@ -10,8 +10,8 @@ from _helpers import u64_host
 
 pytestmark = pytest.mark.gpu
 
-# keys per thread change after 256, 1024, 2048 and 4096 blocks
-SIZES = [1, 2, 255, 256, 257, 1024, 1025, 2048, 2049, 4097, 9000]
+# keys per thread change after 256, 1024, 2048, 4096 and 8192 blocks
+SIZES = [1, 2, 255, 256, 257, 1024, 1025, 2048, 2049, 4097, 8192, 9000]
 
 
 def _scores(kind, rng, shape):
@@ -21,6 +21,12 @@ def _scores(kind, rng, shape):
         s[...] = 1.25
     elif kind == "outlier":        # one far score: the rest in one bucket
         s[..., rng.integers(n)] = 1e20
+    elif kind == "outliers":       # and one far from the next: bucket after bucket
+        s[..., :8] = np.float32(10.0) ** np.arange(4, 36, 4)[:min(n, 8)]
+    elif kind == "scales":         # every scale of float32, both signs
+        s = (np.sign(s) * 2.0 ** rng.integers(-140, 127, s.shape)).astype(np.float32)
+    elif kind == "few":            # a few values: more ties than a bucket ranks
+        s = np.round(2 * s).astype(np.float32)
     elif kind == "clusters":       # buckets of many nearly equal keys
         s = (np.round(s) + 1e-4 * s).astype(np.float32)
     elif kind == "huge":           # the range overflows float32
@@ -34,8 +40,8 @@ def _scores(kind, rng, shape):
     return s
 
 
-@pytest.mark.parametrize("kind", ["normal", "equal", "outlier", "clusters", "huge", "tiny",
-                                  "infinite"])
+@pytest.mark.parametrize("kind", ["normal", "equal", "outlier", "outliers", "scales", "few",
+                                  "clusters", "huge", "tiny", "infinite"])
 @pytest.mark.parametrize("nc", SIZES)
 def test_select_is_exact(kind, nc):
     rng = np.random.default_rng(nc)
