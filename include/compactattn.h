@@ -267,14 +267,16 @@ ca_status ca_estimate_tables(const ca_problem* p, const uint16_t* q, const uint1
  *    num_splits: 1 = one pass per query tile; > 1 = the table of each row is
  *    cut into that many consecutive pieces whose partial results are merged
  *    by log-sum-exp (needs workspace); 0 = let the library choose:
- *      - for short rows and chunks with much of a causal triangle: query tiles
- *        of half the size, two to a CU, no row cut (no workspace is needed);
- *      - when fewer than 32 query tiles share at most 64 table rows and there
- *        is work for every CU (about 4 expected pages each) and the workspace
- *        holds ca_attention_workspace_bytes(p, group_size, 0): one workgroup
- *        per CU, each running an equal share of the pages, computed on the GPU
- *        from the table lengths (not where uniform splits are as even: see
- *        attn_shares in csrc/kernels.hpp); a second launch merges the pieces;
+ *      - half tiles, for short rows and for chunks with much of a causal triangle:
+ *        query tiles of half the size, two to a CU, no row cut (no workspace is
+ *        needed);
+ *      - equal shares, when fewer than 32 query tiles share at most 64 table rows,
+ *        there is work for every CU (about 4 expected pages each), other launches
+ *        are expected to leave CUs idle for longer than more pieces take, and the
+ *        workspace holds ca_attention_workspace_bytes(p, group_size, 0): one
+ *        workgroup per CU, each running an equal share of the pages, computed on
+ *        the GPU from the table lengths; a second launch merges the pieces
+ *        (attn_choice in csrc/kernels.hpp chooses between these and the next);
  *      - when the query tiles fill the GPU, B * G is a multiple of 8 and the
  *        workspace holds ca_attention_workspace_bytes(p, group_size, 0):
  *        every table row is cut in two at a point computed on the GPU from

@@ -112,10 +112,7 @@ int auto_splits(const ca::Dims& d, int group_size, size_t ws_bytes, bool have_ws
   const int base = ca::attn_base_workgroups(d, group_size, table_mode);
   const int target = ca::attn_resident_workgroups(table_mode);
   if (base >= target || !have_ws) return 1;
-  int s = (target + base - 1) / base;
-  const int max_by_len = d.max_nkb / 4 > 1 ? d.max_nkb / 4 : 1;
-  if (s > max_by_len) s = max_by_len;
-  if (s > ca::kMaxUniformSplits) s = ca::kMaxUniformSplits;
+  int s = ca::attn_uniform_splits(base, target, d.max_nkb);
   while (s > 1 && ca::attn_ws_bytes(d, s) > ws_bytes) --s;
   return s < 1 ? 1 : s;
 }
@@ -139,6 +136,35 @@ bool xcd_balance_ok(const ca::Dims& d, const ca_problem* p, int group_size, int 
     return false;
   }
   return true;
+}
+
+// The launch of an attention call (num_splits = 0: the library's choice).
+struct LaunchChoice {
+  bool half = false;       // half tiles
+  ca::AttnShares shares;   // .on: equal shares per CU
+  bool xcd = false;        // two pieces per row, balanced over the XCDs
+  int splits = 1;
+};
+LaunchChoice choose_launch(const ca_problem* p, const ca::Dims& d, int group_size, int table_mode,
+                           bool dense, const void* ws, size_t ws_bytes) {
+  LaunchChoice c;
+  if (table_mode != ca::kTablesPerQTile) {
+    const ca::AttnSize z = ca::attn_size(d.B, d.Hq / group_size, group_size, d.C, d.page,
+                                         p->cached_len_host, dense);
+    const ca::AttnChoice choice = ca::attn_choice(z, d.D);
+    c.half = choice == ca::AttnChoice::kHalfTiles;
+    // with too little workspace (or an unaligned one) the launches below, as they take it
+    if (choice == ca::AttnChoice::kShares && ws != nullptr &&
+        reinterpret_cast<uintptr_t>(ws) % 16 == 0) {
+      const ca::AttnShares s = ca::attn_shares(z, d.C, d.D);
+      if (ws_bytes >= ca::attn_shares_ws_bytes(d, group_size, s)) c.shares = s;
+    }
+  }
+  if (c.half || c.shares.on) return c;
+  c.xcd = xcd_balance_ok(d, p, group_size, table_mode, dense) && ws != nullptr &&
+          ws_bytes >= ca::attn_xcd_ws_bytes(d, group_size);
+  c.splits = c.xcd ? 2 : auto_splits(d, group_size, ws_bytes, ws != nullptr, table_mode);
+  return c;
 }
 
 // The kernels read and write the bf16 and fp32 tensors with 16-byte vector
@@ -333,25 +359,10 @@ ca_status run_attention(const ca_problem* p, const uint16_t* q, const uint16_t* 
   if ((s = attention_tile_ok(group_size, table_mode)) != CA_OK) return s;
   if (num_splits < 0 || num_splits > 64)
     return fail(CA_ERR_SHAPE, "num_splits %d out of range [0, 64]", num_splits);
-  int splits = num_splits;
-  bool xcd = false;
-  ca::AttnShares shares;
-  bool half = false;
-  if (splits == 0) {
-    half = table_mode != ca::kTablesPerQTile &&
-           ca::attn_half_tiles(d, group_size, p->cached_len_host, dense);
-    // equal shares per CU; with too little workspace (or an unaligned one) the
-    // launches below, as they take it
-    if (!half && table_mode != ca::kTablesPerQTile && ws != nullptr &&
-        reinterpret_cast<uintptr_t>(ws) % 16 == 0) {
-      shares = ca::attn_shares(d, group_size, p->cached_len_host, dense);
-      if (shares.on && ws_bytes < ca::attn_shares_ws_bytes(d, group_size, shares))
-        shares.on = false;
-    }
-    xcd = !half && !shares.on && xcd_balance_ok(d, p, group_size, table_mode, dense) && ws != nullptr &&
-          ws_bytes >= ca::attn_xcd_ws_bytes(d, group_size);
-    splits = half || shares.on ? 1 : xcd ? 2 : auto_splits(d, group_size, ws_bytes, ws != nullptr, table_mode);
-  }
+  LaunchChoice c;
+  c.splits = num_splits;
+  if (num_splits == 0) c = choose_launch(p, d, group_size, table_mode, dense, ws, ws_bytes);
+  const int splits = c.splits;
   if (splits > 1) {
     const size_t need = ca::attn_ws_bytes(d, splits);
     if (ws == nullptr || ws_bytes < need)
@@ -373,9 +384,9 @@ ca_status run_attention(const ca_problem* p, const uint16_t* q, const uint16_t* 
   L.group_size = group_size;
   L.sm_scale = sm_scale;
   L.splits = splits;
-  L.xcd_balanced = xcd;
-  L.shares = shares;
-  L.half_tiles = half;
+  L.xcd_balanced = c.xcd;
+  L.shares = c.shares;
+  L.half_tiles = c.half;
   L.ws = ws;
   L.dense = dense;
   L.table_mode = table_mode;
@@ -700,22 +711,42 @@ size_t ca_attention_workspace_bytes(const ca_problem* p, int32_t group_size, int
   if (num_splits < 0 || num_splits > 64) return 0;
   int s = num_splits;
   if (s == 0) {
+    if (ca::attn_query_tile(group_size, ca::kTablesPerGroup) < 1) return 0;   // refused by the calls
     // room for the XCD-balanced split, or for the splits chosen without it
     const size_t uni = ca::attn_ws_bytes(d, auto_splits(d, group_size, (size_t)-1, true));
     const size_t bal = xcd_balance_ok(d, p, group_size, ca::kTablesPerGroup, false)
                            ? ca::attn_xcd_ws_bytes(d, group_size)
                            : 0;
     size_t need = bal > uni ? bal : uni;
-    // or for equal shares per CU, of the selected tables or the dense ones
+    // or for equal shares per CU where they are chosen, for the selected tables or the dense ones
     for (const bool dense : {false, true}) {
-      const size_t sh = ca::attn_shares_ws_bytes(
-          d, group_size, ca::attn_shares(d, group_size, p->cached_len_host, dense));
+      const ca::AttnSize z = ca::attn_size(d.B, d.Hq / group_size, group_size, d.C, d.page,
+                                           p->cached_len_host, dense);
+      if (ca::attn_choice(z, d.D) != ca::AttnChoice::kShares) continue;
+      const size_t sh = ca::attn_shares_ws_bytes(d, group_size, ca::attn_shares(z, d.C, d.D));
       need = sh > need ? sh : need;
     }
     return need;
   }
   return ca::attn_ws_bytes(d, s);
 }
+
+#ifdef CA_DEBUG_CHECKS
+// Debug library only, for tests: the launch that num_splits = 0 takes with a
+// workspace of ws_bytes.  1 half tiles, 2 equal shares, 3 the XCD cut, 16 + s: s
+// uniform splits; 0 for a problem that is refused.  Needs no GPU.
+int ca_debug_attention_launch(const ca_problem* p, int32_t group_size, int32_t dense,
+                              size_t ws_bytes) {
+  ca::Dims d;
+  if (group_size < 1 || check(p, group_size, &d) != CA_OK ||
+      attention_tile_ok(group_size, ca::kTablesPerGroup) != CA_OK)
+    return 0;
+  alignas(16) static char some[16];   // stands for a workspace; not read
+  const LaunchChoice c = choose_launch(p, d, group_size, ca::kTablesPerGroup, dense != 0,
+                                       ws_bytes > 0 ? some : nullptr, ws_bytes);
+  return c.half ? 1 : c.shares.on ? 2 : c.xcd ? 3 : 16 + c.splits;
+}
+#endif
 
 ca_status ca_chunk_attention(const ca_problem* p, const uint16_t* q, const uint16_t* k_pool,
                              const uint16_t* v_pool, const int32_t* page_table,

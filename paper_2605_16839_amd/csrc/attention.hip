@@ -1704,13 +1704,6 @@ size_t attn_xcd_ws_bytes(const Dims& d, int group_size) {
          (size_t)attn_base_workgroups(d, group_size, kTablesPerGroup) * 8;
 }
 
-AttnShares attn_shares(const Dims& d, int group_size, const int32_t* cached_len_host, bool dense) {
-  const int QT = attn_query_tile(group_size, kTablesPerGroup);
-  if (QT < 1) return {};   // not a tile the kernels run (refused before a launch)
-  return attn_shares(d.B, d.Hq / group_size, d.C, (d.C + QT - 1) / QT, QT, d.D, kPage,
-                     cached_len_host, dense);
-}
-
 // Half tiles: 128 rows per workgroup, so that two workgroups share a CU and the
 // causal triangle (tile t of a chunk sees t more steps of the cache than tile 0)
 // evens out: tiles n-1-k and k start beside each other, and a CU whose short
@@ -1724,33 +1717,9 @@ AttnShares attn_shares(const Dims& d, int group_size, const int32_t* cached_len_
 //   chunk 2048 over 16384, dense       450.9 -> 452.5    chunk 1500  50.0 -> 39.9
 //   chunk 500 over 4000, dense          50.5 -> 71.6 (71 pages alone on a CU
 //                                       against four pieces: not chosen)
-// The rule.  Where whole tiles fill the GPU: a triangle of 9% of the pages or
-// more.  Else the times that fit the measured ones: a start of 11 us and 1.0 us
-// per page of the longest row, or 1.1 per page and CU; against 22 us for a start
-// and a merge and 1.85 us per page of 256 rows and CU.  D = 64: 0.6 of a page.
-bool attn_half_tiles(const Dims& d, int group_size, const int32_t* cached_len_host, bool dense) {
-  const int qt = attn_query_tile(group_size, kTablesPerGroup);
-  const int qt_half = attn_query_tile(group_size, kTablesPerQTile);
-  if (qt_half < 1 || attn_rows_per_workgroup(kTablesPerQTile) % group_size != 0) return false;
-  const int n = (d.C + qt - 1) / qt, n_half = (d.C + qt_half - 1) / qt_half;
-  const int G = d.Hq / group_size;
-  const double cus = kXcds * kCusPerXcd;
-  // pages a tile does not see, on average over the tiles
-  const double unseen = (n - 1) * (qt / (double)kPage) / 2;
-  const double unseen_half = (n_half - 1) * (qt_half / (double)kPage) / 2;
-  double longest = 0, line = 0, full = 0, half = 0;
-  for (int b = 0; b < d.B; ++b) {
-    const int nc = cached_len_host[b] / kPage, nkb = blocks_for(cached_len_host[b] + d.C);
-    const double len = dense ? nkb : nkb - nc + expected_listed(nc);
-    longest = len > longest ? len : longest;
-    line += G * len;
-    full += G * n * (len - unseen) / cus;
-    half += G * n_half * (len - unseen_half) / cus;
-  }
-  if ((double)d.B * G * n >= cus) return d.B * G * unseen >= 0.09 * line;
-  const double page = d.D == 64 ? 0.6 : 1.0;
-  return 11 + page * (longest > 1.1 * half ? longest : 1.1 * half) < 22 + 1.85 * page * full;
-}
+static_assert(kAttnTileRows == 16 * kColTiles * kWavesGroup &&
+                  kAttnHalfTileRows == 16 * kColTiles * kWavesQTile,
+              "the choice of a launch counts the kernels' tiles");
 
 // Workspace of a balanced launch: the partial results and log-sum-exps of its
 // slots (fp32), then the piece list of every (row, tile).

@@ -223,62 +223,182 @@ __host__ __device__ __forceinline__ int share_visible(int len, int cached_len, i
   return len - unseen > 1 ? len - unseen : 1;
 }
 
+// ---------------------------------------------------------------------------
+// Which launch an attention call takes (num_splits = 0).  The tables are on the
+// GPU, so the choice goes by the sizes and the expected table lengths; a result's
+// validity never depends on it.
+// ---------------------------------------------------------------------------
+constexpr int kAttnCus = kAttnXcds * kAttnCusPerXcd;
+constexpr int kAttnTileRows = 256, kAttnHalfTileRows = 128;   // (head, query) rows per workgroup
+constexpr int kMaxUniformSplits = 16;   // of the automatic choice
+
 // Cached blocks that a row's table is expected to list: the paper's executed
 // density after both unions is 0.30 on long contexts; short ones keep more (the
 // forced blocks and the union of few top blocks per row: nearly all of 16).
-// Only the choice between launches depends on it, never a result's validity.
 inline double expected_listed(int cached_blocks) {
   const double n = 16 + 0.3 * cached_blocks;
   return n < cached_blocks ? n : cached_blocks;
 }
-// Fewest expected pages per CU for a balanced launch, where other launches leave
-// CUs idle and where uniform splits fill the GPU evenly.
-constexpr double kBalancedMinPages = 4.0, kBalancedMinPagesEven = 32.0;
-constexpr int kMaxUniformSplits = 16;   // of the automatic choice
-// Where the query tiles alone fill the GPU: the largest part of the pages that
-// the causal triangle may take off the first tiles (the CUs of an XCD then
-// differ by about as much).
-constexpr double kBalancedMaxTriangle = 0.18;
 
-// The shares of a launch over `groups` table rows per sequence and n query
-// tiles, or .on = false where another launch is better.
-inline AttnShares attn_shares(int batch, int groups, int C, int n, int query_tile, int head_dim,
-                              int page, const int* cached_len, bool dense) {
-  AttnShares s;
-  const long long R = (long long)batch * groups;
-  if (R > kSharesMaxRows || n >= kAttnCusPerXcd) return s;
-  double line = 0;   // expected entries of all rows
-  bool equal = true;
+// Uniform splits of `base` tiles that fill the `resident` workgroups of the GPU.
+inline int attn_uniform_splits(int base, int resident, int max_nkb) {
+  if (base >= resident) return 1;
+  int s = (resident + base - 1) / base;
+  const int by_len = max_nkb / 4 > 1 ? max_nkb / 4 : 1;
+  if (s > by_len) s = by_len;
+  return s < kMaxUniformSplits ? s : kMaxUniformSplits;
+}
+
+// Sizes of an attention call as the choice sees them.
+struct AttnSize {
+  int rows;                 // table rows (b, group)
+  int tiles, half_tiles;    // query tiles per row, whole and half
+  int query_tile;           // chunk queries of a whole tile
+  int tile_rows;            // rows of a whole tile that hold a query
+  int splits;               // uniform splits
+  double longest, line;     // expected entries of the longest row and of all rows
+  double full, half;        // pages per CU that whole tiles and half tiles walk
+  double unseen;            // entries that a whole tile does not see, on average
+  double xcd_share;         // pages of the XCD with the most half tiles, over the average
+  bool dense;
+};
+
+inline AttnSize attn_size(int batch, int groups, int group_size, int C, int page,
+                          const int* cached_len, bool dense) {
+  AttnSize z{};
+  z.rows = batch * groups;
+  const int qt = z.query_tile = kAttnTileRows / group_size, qt_half = kAttnHalfTileRows / group_size;
+  z.tiles = (C + qt - 1) / qt;
+  z.half_tiles = qt_half > 0 && kAttnHalfTileRows % group_size == 0 ? (C + qt_half - 1) / qt_half : 0;
+  z.tile_rows = group_size * (C < qt ? C : qt);
+  z.unseen = (z.tiles - 1) * (qt / (double)page) / 2;
+  const double unseen_half = (z.half_tiles - 1) * (qt_half / (double)page) / 2;
+  z.dense = dense;
+  double load[kAttnXcds] = {};
+  int max_nkb = 0;
   for (int b = 0; b < batch; ++b) {
     const int nc = cached_len[b] / page, nkb = (cached_len[b] + C - 1) / page + 1;
-    line += groups * (dense ? nkb : nkb - nc + expected_listed(nc));
-    equal = equal && cached_len[b] == cached_len[0];
+    const double len = dense ? nkb : nkb - nc + expected_listed(nc);
+    z.longest = len > z.longest ? len : z.longest;
+    z.line += groups * len;
+    z.full += groups * z.tiles * (len - z.unseen) / kAttnCus;
+    z.half += groups * z.half_tiles * (len - unseen_half) / kAttnCus;
+    max_nkb = nkb > max_nkb ? nkb : max_nkb;
+    // half tiles of row r run on XCD r % 8 where the rows spread evenly, else the
+    // XCDs take the rows in order, an eighth each
+    for (int r = b * groups; r < (b + 1) * groups; ++r) {
+      const double pages = len > unseen_half + 1 ? len - unseen_half : 1;
+      if (z.rows % kAttnXcds == 0) load[r % kAttnXcds] += pages;
+      else load[(int)((r + 0.5) * kAttnXcds / z.rows)] += pages;
+    }
   }
-  const int cus = kAttnXcds * kAttnCusPerXcd;
-  const double pages = line * n / cus;   // per CU
-  if (pages < kBalancedMinPages) return s;
-  // rows of (about) one length whose tiles fill the GPU by uniform splits
-  if (equal && cus % (R * n) == 0 && cus / (R * n) <= kMaxUniformSplits &&
-      (dense || pages < kBalancedMinPagesEven))
-    return s;
-  if (R * n >= cus &&
-      R * (n - 1) * (query_tile / (double)page) / 2 > kBalancedMaxTriangle * line)
-    return s;
+  double most = 0, all = 0;
+  for (double x : load) {
+    most = x > most ? x : most;
+    all += x;
+  }
+  // a launch that is not a multiple of 8 workgroups is dealt out one by one
+  z.xcd_share = (long long)z.rows * z.half_tiles % kAttnXcds == 0 ? most * kAttnXcds / all : 1;
+  z.splits = attn_uniform_splits(z.rows * z.tiles, kAttnCus, max_nkb);
+  return z;
+}
+
+// Times in us of the launches where the whole tiles leave CUs idle.  The constants
+// were fitted to the choice that they make, over 2900 random sizes with every launch
+// timed (1-8 sequences, 0-130K cached, 1-3000 tokens, 4-64 heads, listed at 0.15-0.5
+// or dense, one GPU): 25 of them then take over 3% longer than with uniform splits
+// and the XCD cut alone (at most 1.25 times), 0.855 of the time in the mean.
+//   half tiles: a start, and the longest row at the rate of a workgroup that is
+//     alone on its CU, or the CU's pages at that of two;
+//   equal shares: a start and the merge launch, the CU's pages, the more pieces
+//     the more tiles, and the partial results of the rows that hold a query;
+//   uniform splits: the same with pieces of the longest row, or where the pieces
+//     outnumber the CUs about one piece more than the average; the merge of more
+//     than 8 pieces goes through them twice.
+struct AttnTimes {
+  double half, shares, uniform;
+};
+inline AttnTimes attn_times(const AttnSize& z, int head_dim) {
+  const bool d64 = head_dim == 64;
+  const double base = z.rows * (double)z.tiles / kAttnCus, held = z.tile_rows / (double)kAttnTileRows;
+  const double alone = (d64 ? 0.6 : 0.87) * z.longest, shared = 0.8 * z.half;
+  const double piece = z.longest / z.splits;
+  const double walked = base * z.splits <= 1 ? piece : z.full + 0.8 * piece;
+  AttnTimes t;
+  t.half = (d64 ? 8 : 11.5) + (alone > shared ? alone : shared);
+  t.shares = d64 ? 16.5 + 1.2 * z.full + 10 * base + 4 * held
+                 : 25 + 1.4 * z.full + 13 * base + 6 * held;
+  t.uniform = d64 ? 12 + 1.0 * walked + 8.5 * base * z.splits * held + (z.splits > 8 ? 10 : 0)
+                  : 17 + 1.4 * walked + 13 * base * z.splits * held + (z.splits > 8 ? 9 : 0);
+  return t;
+}
+
+// Equal shares can be laid out, and every CU has at least 4 expected pages (below
+// that they take as long as the best other launch in the median, 0.65 to 1.4 of it
+// from size to size).
+inline bool attn_shares_fit(const AttnSize& z) {
+  return z.rows <= kSharesMaxRows && z.tiles < kAttnCusPerXcd &&
+         z.line * z.tiles / kAttnCus >= 4.0;
+}
+
+enum class AttnChoice { kHalfTiles, kShares, kOther };   // kOther: the XCD cut or uniform splits
+inline AttnChoice attn_choice(const AttnSize& z, int head_dim) {
+  const bool fit = attn_shares_fit(z);
+  const long long tiles = (long long)z.rows * z.tiles;
+  if (tiles >= kAttnCus) {
+    // Whole tiles fill the GPU.  By the part of the pages that the causal triangle
+    // takes off the first tiles, medians over 112 of those sizes:
+    //                          < 0.03  0.03-  0.06-  0.09-  0.12-  0.18-  0.25-
+    //   half tiles : XCD cut     1.01   0.98   0.96   0.91   0.92   0.89   0.89
+    //   equal shares : XCD cut   0.69   0.82   1.00   1.09   1.08   1.07   1.11
+    // Copying each page for half the rows costs half tiles 3% at 128K.  They are not
+    // cut, so that rows of different lengths leave some XCDs idle: with 1.13-1.54
+    // times the average on one XCD 0.61-0.98 (11 sizes, one 1.03), with 1.99-2.7
+    // times 0.93-1.42.
+    // Equal shares gain what other launches leave idle, about the longest row's
+    // pages in every round of tiles less the average: 0.37-1.0 of their time from
+    // 24 pages (20 of 21 sizes), 0.93-1.12 below (11 sizes, median 1.04), the
+    // 0.93 in four rounds, where the XCD cut makes twice their pieces.
+    const bool much = z.rows * z.unseen >= 0.09 * z.line;
+    if (much && z.half_tiles > 0 && z.xcd_share < 1.75) return AttnChoice::kHalfTiles;
+    const long long rounds = (tiles + kAttnCus - 1) / kAttnCus;
+    return fit && !much && (rounds >= 3 || z.longest * rounds - z.full >= 24)
+               ? AttnChoice::kShares : AttnChoice::kOther;
+  }
+  if (z.splits == 1 && z.half_tiles > 0) return AttnChoice::kHalfTiles;   // at most 7 blocks
+  const AttnTimes t = attn_times(z, head_dim);
+  // Equal shares, but where uniform splits give every CU one piece only if they are
+  // shorter: those are as even by expectation.  Real tables differ from row to row,
+  // and from about 100 pages per CU on that outweighs what more pieces cost (rows
+  // 15% apart: equal shares 1.04-1.11 of the time at 41-95 pages, 1.0 at 130 and 210;
+  // the tables of a real selection at 157 pages: 250 us against 267 for the step).
+  const bool one_each = tiles * z.splits == kAttnCus;
+  const bool shares = fit && (!one_each || t.shares < t.uniform || (!z.dense && z.full >= 100));
+  // 5% for the fit's error: the cut launches lose less where they are wrong
+  if (z.half_tiles > 0 && 1.05 * t.half < (shares ? t.shares : t.uniform))
+    return AttnChoice::kHalfTiles;
+  return shares ? AttnChoice::kShares : AttnChoice::kOther;
+}
+
+// The shares of a launch (attn_shares_fit).
+inline AttnShares attn_shares(const AttnSize& z, int C, int head_dim) {
+  AttnShares s;
+  const int n = z.tiles;
   s.on = true;
   // one tile: its rows packed, so that a tile's rows end with the last query
-  s.query_tile = n == 1 ? C : query_tile;
-  // a piece costs about 12 us, 8 pages of 1.6 us (D = 128); short shares lose
+  s.query_tile = n == 1 ? C : z.query_tile;
+  // a piece costs about 14 us, 8 pages of 1.6 us (D = 128); short shares lose
   // more by rounding to it than the pieces cost
   const int most = head_dim == 64 ? 6 : 8;
-  const double o = pages / (head_dim == 64 ? 8 : 3);
+  const double o = z.line * n / kAttnCus / (head_dim == 64 ? 8 : 3);
   s.overhead = o < 4 ? 4 : o > most ? most : (int)o;
   s.n = n;
   s.s_main = kAttnCusPerXcd / n;
   s.left = kAttnCusPerXcd - n * s.s_main;
   s.slots_per_slab = n * s.s_main + (s.left > 0 ? n + s.left : 0);
-  s.first_by_row = R * n < kAttnXcds * s.slots_per_slab;
+  s.first_by_row = z.rows * n < kAttnXcds * s.slots_per_slab;
   s.slots = kAttnXcds * s.slots_per_slab +
-            (s.first_by_row ? (int)(R * n) : kAttnXcds * s.slots_per_slab);
+            (s.first_by_row ? z.rows * n : kAttnXcds * s.slots_per_slab);
   return s;
 }
 
@@ -309,14 +429,10 @@ struct AttnLaunch {
   bool xcd_balanced = false;
   int v_layout = kVTokenMajor;
   AttnShares shares;   // shares.on: balanced launch (attn_shares_ws_bytes of ws)
-  bool half_tiles = false;   // 128 rows per workgroup, two workgroups per CU; splits == 1
+  // 128 rows per workgroup, two workgroups per CU, so that the causal triangle evens
+  // out and no row is cut; splits == 1 (attention.hip: pair_tiles)
+  bool half_tiles = false;
 };
-// The shares of a balanced launch of these sizes; .on = false where another
-// launch is better.
-AttnShares attn_shares(const Dims& d, int group_size, const int32_t* cached_len_host, bool dense);
-// Whether short rows are better run as tiles of 128 rows, two workgroups to a
-// CU and no row cut (attention.hip).
-bool attn_half_tiles(const Dims& d, int group_size, const int32_t* cached_len_host, bool dense);
 size_t attn_shares_ws_bytes(const Dims& d, int group_size, const AttnShares& s);
 int attn_rows_per_workgroup(int table_mode);             // (head, query) rows per workgroup
 int attn_query_tile(int group_size, int table_mode);     // chunk queries per workgroup

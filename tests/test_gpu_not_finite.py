@@ -17,7 +17,7 @@ LAUNCHES = [
     ((9000,), 300, (8, 2), 128, 4, 2),          # merge of two uniform pieces
     ((9000,), 300, (8, 2), 64, 4, 5),           # all pieces in flight
     ((9000,), 300, (8, 2), 128, 4, 12),         # more pieces than that
-    ((40000,), 37, (8, 2), 128, 4, 0),          # equal shares, four waves to a fragment
+    ((40000,), 37, (32, 8), 128, 4, 0),         # equal shares, four waves to a fragment
     ((20000,), 300, (32, 8), 64, 4, 0),         # equal shares, one wave
     ((30000,), 2048, (32, 8), 64, 4, 0),        # two pieces per row, balanced over the XCDs
 ]

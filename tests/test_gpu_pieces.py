@@ -72,30 +72,53 @@ def test_trailing_entries_past_one_window(chunk_open):
 
 # Launches that share their pages equally among the CUs, around the edges of the
 # schedule: one query tile (32 segments per slab) to 31 tiles (one segment and a
-# remainder on one CU), flat shares of a causal triangle, rows of very different
-# lengths, and rows that list few blocks or none.
+# remainder on one CU), one table row, rows of very different lengths, selected and
+# dense tables of both head sizes and V layouts.  (test_launch_choice.py checks that
+# the sizes of each list take the launch it names.)
 SHARES = [
     # cached, chunk, heads, dim, group, layout, density (None = dense)
     ((40000,), 37, (32, 8), 64, 4, 0, 0.3),
     ((40000,), 1, (32, 8), 128, 4, 1, 0.3),
     ((20000,), 300, (32, 8), 128, 4, 0, 0.4),
     ((9000,), 700, (32, 8), 64, 4, 1, 0.5),
-    ((7001,), 1451, (32, 8), 128, 4, 0, 0.6),
-    ((5000,), 1984, (16, 4), 64, 4, 1, 0.6),
+    ((7001,), 1451, (16, 4), 128, 4, 0, 0.6),
+    ((9000,), 1984, (16, 4), 128, 4, 1, 0.6),
     ((9000, 37, 30000), 200, (32, 8), 64, 4, 0, 0.4),
-    ((6000, 12000), 500, (8, 1), 64, 8, 1, 0.5),
     ((6000,), 700, (16, 8), 128, 2, 0, 0.4),
     ((30000,), 999, (4, 1), 64, 4, 0, 0.9),
-    ((3000,), 1024, (32, 8), 64, 4, 1, 0.5),
-    ((0,), 2048, (32, 8), 128, 4, 0, None),
-    ((0, 500), 1000, (32, 8), 64, 4, 1, None),
     ((100, 3000, 0), 777, (16, 4), 128, 4, 0, None),
+    ((16384,), 64, (32, 8), 128, 4, 1, None),
+    ((8192,), 1200, (32, 8), 64, 4, 0, None),
+    ((6000,), 700, (16, 4), 64, 4, 1, None),
+    ((20000,), 300, (4, 1), 64, 4, 1, None),
+]
+# Uniform splits, some of more pieces than the merge holds at once.
+UNIFORM = [
+    ((6000, 12000), 500, (8, 1), 64, 8, 1, 0.5),
+    ((9000,), 512, (32, 8), 64, 4, 1, 0.5),
     ((9000,), 999, (16, 4), 64, 4, 0, None),
+    ((30000,), 300, (4, 1), 64, 4, 0, 0.4),
 ]
 
 
 @pytest.mark.parametrize("cached,chunk,heads,dim,group,layout,density", SHARES)
 def test_equal_shares_match_oracle(cached, chunk, heads, dim, group, layout, density):
+    _matches_oracle(cached, chunk, heads, dim, group, layout, density)
+
+
+@pytest.mark.parametrize("cached,chunk,heads,dim,group,layout,density", UNIFORM)
+def test_uniform_splits_match_oracle(cached, chunk, heads, dim, group, layout, density):
+    _matches_oracle(cached, chunk, heads, dim, group, layout, density)
+
+
+@pytest.mark.parametrize("short", [1, 16])
+def test_equal_shares_without_their_workspace(short):
+    """A workspace too small for the equal shares by a byte, or by its alignment:
+    another launch, the same result."""
+    _matches_oracle(*SHARES[2], short=short)
+
+
+def _matches_oracle(cached, chunk, heads, dim, group, layout, density, short=0):
     w, d = _inputs(cached, chunk, heads, dim)
     w = synth.configs.replace(w, group_size=group)
     x = device_inputs(d, layout)
@@ -107,7 +130,7 @@ def test_equal_shares_match_oracle(cached, chunk, heads, dim, group, layout, den
     lse = torch.empty((w.batch, heads[0], chunk), dtype=torch.float32, device="cuda")
 
     def run(fill):
-        ws = torch.full((max(n, 16),), fill, dtype=torch.uint8, device="cuda")
+        ws = torch.full((max(n - short, 16),), fill, dtype=torch.uint8, device="cuda")
         lse.fill_(float("nan"))
         out = torch.full_like(q, float("nan"))
         if density is None:
@@ -152,6 +175,10 @@ def test_equal_shares_sparse_rows(chunk):
 # not spread over the XCDs evenly, unaligned lengths, selected and packed tables.
 HALF = [
     # cached, chunk, heads, dim, group, layout, density (None = dense)
+    ((0,), 2048, (32, 8), 128, 4, 0, None),
+    ((0, 500), 1000, (32, 8), 64, 4, 1, None),
+    ((3000,), 1024, (32, 8), 64, 4, 1, 0.5),
+    ((7001,), 1451, (32, 8), 128, 4, 0, 0.6),
     ((0,), 1, (4, 1), 64, 4, 0, None),
     ((0,), 64, (32, 8), 128, 4, 0, None),
     ((0,), 97, (32, 8), 128, 4, 1, None),
@@ -169,12 +196,17 @@ HALF = [
 
 @pytest.mark.parametrize("cached,chunk,heads,dim,group,layout,density", HALF)
 def test_half_tiles_match_oracle(cached, chunk, heads, dim, group, layout, density):
-    test_equal_shares_match_oracle(cached, chunk, heads, dim, group, layout, density)
+    _matches_oracle(cached, chunk, heads, dim, group, layout, density)
 
 
-def test_half_tiles_sparse_rows():
+# cached, chunk: short rows, and whole tiles that fill the GPU
+SPARSE_HALF = [((900,), 600), ((3000,), 2048)]
+
+
+@pytest.mark.parametrize("cached,chunk", SPARSE_HALF)
+def test_half_tiles_sparse_rows(cached, chunk):
     """Rows that leave out chunk blocks or list nothing; no workspace at all."""
-    w, d = _inputs((900,), 600, (32, 8))
+    w, d = _inputs(cached, chunk, (32, 8))
     x = device_inputs(d)
     p = ca.Problem.from_workload(w)
     rows, _, _ = _tables(w, 0.5, 13, chunk_open=False)
@@ -182,7 +214,7 @@ def test_half_tiles_sparse_rows():
     ip = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
     ix = np.zeros(len(rows) * w.max_kv_blocks, dtype=np.int32)
     ix[:ip[-1]] = np.concatenate(rows)
-    lse = torch.full((1, 32, 600), float("nan"), device="cuda")
+    lse = torch.full((1, 32, chunk), float("nan"), device="cuda")
     out = torch.full_like(x["q"], float("nan"))
     ip_dev, ix_dev = i32_dev(ip), i32_dev(ix)
     st = ca.load().ca_chunk_attention(

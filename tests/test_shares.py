@@ -40,8 +40,10 @@ int main(int argc, char** argv) {
     std::vector<int> cl(batch);
     for (int& v : cl) v = pick(0, 2) ? pick(0, 6000) : pick(0, 131072);
     const int D = pick(0, 1) ? 64 : 128;
-    const AttnShares s = attn_shares(batch, groups, C, n, QT, D, page, cl.data(), dense);
-    if (!s.on) continue;
+    const AttnSize z = attn_size(batch, groups, gs, C, page, cl.data(), dense);
+    if (z.tiles != n || z.query_tile != QT) die("tiles");
+    if (!attn_shares_fit(z)) continue;
+    const AttnShares s = attn_shares(z, C, D);
     ++used;
     (s.left ? uneven : even)++;
     const int R = batch * groups;
