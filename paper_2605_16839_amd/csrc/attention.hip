@@ -1203,16 +1203,18 @@ __device__ __forceinline__ void attend(const AttnArgs& a) {
   if constexpr (BAL) {
     // as the registers lie: fragment (x, c) of a wave is 64 float4, so that a
     // store writes 1 KB in one run and combine_pieces_kernel reads it so (rows
-    // of D floats made 16 runs of 64 bytes of it)
+    // of D floats made 16 runs of 64 bytes of it).  A slot holds the column
+    // tiles with a query: the first slot_rows / 16 of the workgroup's
     const size_t slot = walk.list.slot(walk.ordinal, rowid * a.n_qtiles + qt, a.shares);
-    float4* po = reinterpret_cast<float4*>(a.part_o) + (slot * NW + wv) * (NDT * NCT * 64) + lane;
-    float* pl = a.part_lse + slot * ROWS + wv * 16 * NCT + col;
+    const int tiles = a.shares.slot_rows / 16, tile0 = wv * NCT;
+    float4* po = reinterpret_cast<float4*>(a.part_o) + (slot * tiles + tile0) * (NDT * 64) + lane;
+    float* pl = a.part_lse + (slot * tiles + tile0) * 16 + col;
 #pragma unroll
     for (int c = 0; c < NCT; ++c) {
       if (__ballot(valid[c]) == 0) continue;
 #pragma unroll
       for (int x = 0; x < NDT; ++x)
-        po[(x * NCT + c) * 64] = make_float4(o[x][c][0] * inv[c], o[x][c][1] * inv[c],
+        po[(c * NDT + x) * 64] = make_float4(o[x][c][0] * inv[c], o[x][c][1] * inv[c],
                                              o[x][c][2] * inv[c], o[x][c][3] * inv[c]);
       if (grp == 0) pl[16 * c] = lse_val[c];
     }
@@ -1584,7 +1586,6 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
 template <int D, int PAR>
 __global__ __launch_bounds__(256) void combine_pieces_kernel(const AttnArgs a) {
   constexpr int NDT = D / 16, FRAGS = NDT * kColTiles, NW = kWavesGroup;
-  constexpr int ROWS = 16 * kColTiles * NW;
   const int w = threadIdx.x >> 6, p = w % PAR;
   const int unit = blockIdx.x * (4 / PAR) + w / PAR;   // (row, tile, wave, fragment)
   const int f = unit % FRAGS, wv = (unit / FRAGS) % NW, tile = unit / (FRAGS * NW);
@@ -1599,6 +1600,9 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(const AttnArgs a) {
   const bool valid = row < a.group_size * QT && tq < a.C;
   // with PAR = 4 the workgroup has one fragment: it leaves as a whole
   if (list.pieces == 1 || __ballot(valid) == 0) return;
+  // the fragment and the row in a slot of slot_rows rows
+  const int slot_tiles = a.shares.slot_rows / 16;
+  const int in_slot = ((row / 16) * NDT + f / kColTiles) * 64 + lane;
   float mx = -INFINITY, wsum = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
   for (int i0 = p; i0 < list.pieces; i0 += PAR * kCombineInFlight) {
     // a batch of pieces; a batch with a higher maximum rescales what came before
@@ -1608,8 +1612,8 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(const AttnArgs a) {
     for (int k = 0; k < kCombineInFlight; ++k) {
       if (i0 + k * PAR < list.pieces) {
         const size_t sl = list.slot(i0 + k * PAR, tile, a.shares);
-        l[k] = a.part_lse[sl * ROWS + row];
-        v[k] = reinterpret_cast<const float4*>(a.part_o)[(sl * NW + wv) * (FRAGS * 64) + f * 64 + lane];
+        l[k] = a.part_lse[sl * slot_tiles * 16 + row];
+        v[k] = reinterpret_cast<const float4*>(a.part_o)[sl * slot_tiles * (NDT * 64) + in_slot];
       }
     }
 #pragma unroll
@@ -1724,7 +1728,7 @@ static_assert(kAttnTileRows == 16 * kColTiles * kWavesGroup &&
 // Workspace of a balanced launch: the partial results and log-sum-exps of its
 // slots (fp32), then the piece list of every (row, tile).
 static size_t shares_partial_rows(const AttnShares& s) {
-  return (size_t)s.slots * attn_rows_per_workgroup(kTablesPerGroup);
+  return (size_t)s.slots * s.slot_rows;
 }
 
 static size_t shares_lists_at(const Dims& d, const AttnShares& s) {

@@ -98,6 +98,7 @@ struct AttnShares {
   int slots_per_slab = 0;  // intervals of one slab over all tiles
   bool first_by_row = true;   // slots of rows' first pieces: see PieceList
   int slots = 0;           // partial results a launch can store
+  int slot_rows = 0;       // rows of a slot: a tile's 16-row fragments that hold a query
 };
 
 // a / b for a quotient below 2^20 (one step of correction on the float one).
@@ -399,6 +400,7 @@ inline AttnShares attn_shares(const AttnSize& z, int C, int head_dim) {
   s.first_by_row = z.rows * n < kAttnXcds * s.slots_per_slab;
   s.slots = kAttnXcds * s.slots_per_slab +
             (s.first_by_row ? z.rows * n : kAttnXcds * s.slots_per_slab);
+  s.slot_rows = (z.tile_rows + 15) & ~15;
   return s;
 }
 

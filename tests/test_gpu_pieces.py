@@ -130,7 +130,9 @@ def _matches_oracle(cached, chunk, heads, dim, group, layout, density, short=0):
     lse = torch.empty((w.batch, heads[0], chunk), dtype=torch.float32, device="cuda")
 
     def run(fill):
-        ws = torch.full((max(n - short, 16),), fill, dtype=torch.uint8, device="cuda")
+        size = max(n - short, 16)
+        guarded = torch.full((size + 4096,), fill, dtype=torch.uint8, device="cuda")
+        ws = guarded[:size]
         lse.fill_(float("nan"))
         out = torch.full_like(q, float("nan"))
         if density is None:
@@ -142,6 +144,7 @@ def _matches_oracle(cached, chunk, heads, dim, group, layout, density, short=0):
             packed = ca.gather_selected_pages(p, kv, x["pt"], tables, group)
             out2, _ = ca.packed_chunk_attention(p, q, packed, tables, group, w.sm_scale, ws=ws)
             assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
+        assert (guarded[size:] == fill).all()     # nothing past the workspace
         return out, lse.clone()
 
     out, l0 = run(0)

@@ -93,3 +93,14 @@ def test_no_shares_workspace_for_half_tiles():
     p = _problem((0, 0), 700, (32, 8), 64)
     rows = 2 * 32 * 700
     assert ca.attention_workspace_bytes(p, 4, 0) == 2 * rows * 65 * 4   # 176 tiles: 2 splits
+
+
+@pytest.mark.parametrize("chunk,rows", [(1, 16), (4, 16), (5, 32), (37, 160), (64, 256)])
+def test_slots_hold_the_rows_of_the_chunk(launch, chunk, rows):
+    """One query tile: a partial result has the 16-row fragments with a query, not
+    the 256 rows of the workgroup (a 34.9 MB workspace for one token over 64K)."""
+    assert launch((65536,), chunk, (32, 8), 128, 4, False) == SHARES
+    slots = 256 + 8     # a piece that goes on from another per CU, a first one per row
+    partial = (slots * rows * 129 * 4 + 15) & ~15
+    assert ca.attention_workspace_bytes(_problem((65536,), chunk, (32, 8), 128), 4, 0) == \
+        partial + 8 * 16
