@@ -139,12 +139,16 @@ def _ptr(t: Optional[torch.Tensor]):
     return ctypes.c_void_p(t.data_ptr())
 
 
+# the current stream's handle without building a Stream object for every call (0.4
+# us against 2.9); a private name of torch, so it may be missing
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
-    if stream is not None:
-        return ctypes.c_void_p(stream.cuda_stream)
-    # the current device's current stream, as torch.cuda.current_stream() finds
-    # it, without building a Stream object for every call (2.9 us against 0.4)
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    if stream is None and _raw_stream is not None:
+        # as torch.cuda.current_stream() finds it: the current device's
+        return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
+    return ctypes.c_void_p((stream or torch.cuda.current_stream()).cuda_stream)
 
 
 class Problem:

@@ -367,3 +367,22 @@ def test_check_tables_host_block_sparse_rows(lib):
     assert _table_status(p, 0, ip, ix, q, 32) == 7
     q = pt.copy(); q[1, 1, 1] = 40                           # block 1: listed by no row
     assert _table_status(p, 0, ip, ix, q, 32) == 0
+
+
+def test_stream_without_torchs_private_name(monkeypatch):
+    """The stream handle comes from torch.cuda.current_stream() where torch has no raw
+    getter, and from the given stream always."""
+    from paper_2605_16839_amd import binding
+
+    class Stream:
+        def __init__(self, handle):
+            self.cuda_stream = handle
+
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda: Stream(4242))
+    monkeypatch.setattr(binding.torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 1000 + device)
+    assert binding._stream().value == 1003
+    assert binding._stream(Stream(77)).value == 77
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    assert binding._stream().value == 4242
+    assert binding._stream(Stream(77)).value == 77
