@@ -587,11 +587,15 @@ hipError_t launch_pool(const Dims& d, const uint16_t* q, float* q_mean, const ui
   const long long nwg = (long long)a.n_q_wg + (long long)a.k_tiles * d.B * d.Hkv;
   if (nwg == 0) return hipSuccess;
   if (nwg > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  // K pages that could not stay in the 256 MB last-level cache are streamed
-  // past it (non-temporal): 128K tokens of 8 heads (268 MB, other pools used in
-  // between) 70 -> 63 us for the whole selection, four sequences (474 MB) 138 ->
-  // 127 us; what fits is faster through it when it is read again (57 MB 34
-  // against 36 us).  A step's attention takes as long after either.
+  // K pages that could not stay in the 256 MB last-level cache are streamed past
+  // it (non-temporal).  Pooling alone in us, cached : streamed, after 800 MB of
+  // other data and again at once (8 heads, D = 128):
+  //   63 MB 24.7 : 17.8, 15.2 : 12.4     252 MB 75.7 : 49.5, 42.7 : 46.5
+  //  131 MB 43.7 : 29.1, 25.3 : 25.2     256 MB 76.4 : 51.2, 42.8 : 48.5
+  //  199 MB 61.3 : 40.4, 34.5 : 37.1     316 MB 89.7 : 61.1, 64.1 : 58.6
+  // Past the cache streaming is faster either way; below it only where other data
+  // went through the cache since, which the call cannot know: pages that are read
+  // again at once stay cached.  A step's attention takes as long after either.
   size_t k_bytes = 0;
   for (int b = 0; b < d.B && k_pool != nullptr; ++b) {
     const int blocks = blocks_for(cached_len_host[b] + d.C) - first_block;
