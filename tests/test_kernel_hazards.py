@@ -11,10 +11,12 @@ registers, counting one wait state per instruction and N+1 per `s_nop N`.
 The bar is the length of the kernel's own fence (21 wait states), above what
 CDNA3 requires after the longest (16-pass) XDL operation.
 """
+import functools
 import os
 import re
 import shutil
 import subprocess
+import tempfile
 
 import pytest
 
@@ -94,20 +96,27 @@ def _shortest_use(lines, labels, k):
     return best
 
 
+@functools.lru_cache(maxsize=None)
+def _compiled(col_tiles: int) -> str:
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "attention.s")
+        cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature",
+               "-Xclang", "-packed-fp32-ops", "--cuda-device-only", "-S",
+               f"-DCA_COL_TILES={col_tiles}",
+               "-I", os.path.join(ROOT, "include"), "-o", out, SRC]
+        r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return open(out).read()
+
+
 @pytest.fixture(scope="module", params=[2, 4])
-def attention_asm(request, tmp_path_factory):
+def attention_asm(request):
     """The kernel's gfx950 assembly as built (two waves per SIMD, 2 column tiles
-    per wave) and in its one-wave form (CA_COL_TILES=4)."""
+    per wave) and in its one-wave form (CA_COL_TILES=4), compiled once for every
+    module that checks it."""
     if not os.path.exists(HIPCC):
         pytest.skip("hipcc not available")
-    out = tmp_path_factory.mktemp("asm") / "attention.s"
-    cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature",
-           "-Xclang", "-packed-fp32-ops", "--cuda-device-only", "-S",
-           f"-DCA_COL_TILES={request.param}",
-           "-I", os.path.join(ROOT, "include"), "-o", str(out), SRC]
-    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
-    assert r.returncode == 0, r.stderr[-2000:]
-    return out.read_text()
+    return _compiled(request.param)
 
 
 def test_mfma_results_wait_before_use(attention_asm):
