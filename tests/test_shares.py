@@ -30,7 +30,7 @@ struct Piece { int e0, e1, pieces, slot; };
 int main(int argc, char** argv) {
   std::mt19937 rng(atoi(argv[1]));
   auto pick = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
-  int used = 0, even = 0, uneven = 0;
+  int used = 0, even = 0, uneven = 0, tight = 0;
   for (int trial = 0; trial < 3000; ++trial) {
     const int gs_of[] = {1, 2, 4, 8};
     const int gs = gs_of[pick(0, 3)], groups = pick(1, 9), batch = pick(1, 7), QT = 256 / gs;
@@ -115,17 +115,28 @@ int main(int argc, char** argv) {
         if (at != len[r]) die("row end");
         if (k != it->second.begin()->second.pieces) die("count");
       }
-    // the CUs' shares differ by the causal triangle (at most the chunk's
-    // blocks per row end), by what a row's cost moves, and by the rounding of
-    // cuts to pairs and row ends
-    double share = 0;
-    for (unsigned v : T) share += v / 256.0;
+    // No CU runs much more than an equal part of the longest tile's line (the
+    // lines differ by the causal triangle), in entries and piece costs o:
+    //   an interval is that long but for what the last segments leave out, 2 o, or
+    //   2 n / left o where there is no last segment (its room is not positive);
+    //   its first row costs o again where it goes on, or begins up to 2 o earlier,
+    //   and its last one ends up to o and a pair later: 3 o + 2;
+    //   a left-over CU has up to n / left + 2 such intervals, o more in length.
+    const int left = s.left;
+    double longest = 0, sum = 0;
+    for (unsigned v : T) longest = std::max(longest, v * n / 256.0), sum += v / 256.0;
+    const double slack = s.overhead * (left ? std::max(2.0, 2.0 * n / left) + 1 : 0) + 3 +
+                         (left ? n / left + 2 : 1) * (3 * s.overhead + 2);
     const long long most = *std::max_element(load.begin(), load.end());
-    if (most > 1.05 * share + (C / page + 2) * (R / 8 + 2) + 10 * s.overhead + 2 * (n + 2) + 4)
-      die("share");
+    if (most > longest + slack) die("share");
+    // long lines: within 1.3 of the equal part of all lines
+    if (sum >= 160 && longest <= 1.05 * sum) {
+      ++tight;
+      if (most > 1.3 * sum) die("long share");
+    }
   }
-  printf("OK %d launches, %d even, %d uneven\n", used, even, uneven);
-  return used > 500 && even > 50 && uneven > 50 ? 0 : 2;
+  printf("OK %d launches, %d even, %d uneven, %d long\n", used, even, uneven, tight);
+  return used > 500 && even > 50 && uneven > 50 && tight > 100 ? 0 : 2;
 }
 """
 
