@@ -746,6 +746,18 @@ int ca_debug_attention_launch(const ca_problem* p, int32_t group_size, int32_t d
                                        ws_bytes > 0 ? some : nullptr, ws_bytes);
   return c.half ? 1 : c.shares.on ? 2 : c.xcd ? 3 : 16 + c.splits;
 }
+
+// Debug library only, for tests: q[i] = share_div(a[i], b[i]) as the GPU computes it.
+__global__ void debug_share_div_kernel(const uint32_t* a, const uint32_t* b, uint32_t* q, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) q[i] = ca::share_div(a[i], b[i]);
+}
+ca_status ca_debug_share_div(const uint32_t* a, const uint32_t* b, uint32_t* q, int32_t n,
+                             void* stream) {
+  if (n < 1) return fail(CA_ERR_SHAPE, "n must be >= 1");
+  debug_share_div_kernel<<<(n + 255) / 256, 256, 0, static_cast<hipStream_t>(stream)>>>(a, b, q, n);
+  return hip_status(hipGetLastError(), "debug_share_div launch");
+}
 #endif
 
 ca_status ca_chunk_attention(const ca_problem* p, const uint16_t* q, const uint16_t* k_pool,

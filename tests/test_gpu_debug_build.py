@@ -147,3 +147,27 @@ def test_debug_library_block_sparse_and_packed(dbg, workload_inputs, oracle_esti
         assert st == 0, (st, lib.ca_last_error_detail())
         outs.append(out)
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
+def test_share_division_on_the_gpu(dbg):
+    """The reciprocal and its one step of correction that every cut of the equal
+    shares goes through, against integer division: dividends up to 8 lines of 64 rows
+    x (16384 entries + 8), quotients below 2^20, at and beside multiples."""
+    import ctypes
+    rng = np.random.default_rng(5)
+    most, n = 8 * 64 * (16384 + 8), 1 << 21
+    b = np.concatenate([rng.integers(1, 65, n), rng.integers(1, most // 8, n),
+                        np.exp(rng.uniform(0, np.log(most), 2 * n)).astype(np.int64)])
+    k = np.exp(rng.uniform(0, np.log(2.0 ** 20), b.size)).astype(np.int64)
+    a = np.where(rng.random(b.size) < 0.75, k * b + rng.integers(-1, 2, b.size),
+                 rng.integers(0, most + 1, b.size))
+    a = np.clip(a, 0, np.minimum(most, b * (2 ** 20 - 1)))
+    da, db = (torch.from_numpy(x.astype(np.int32)).cuda() for x in (a, b))
+    q = torch.full_like(da, -1)
+    fn = dbg.ca_debug_share_div
+    fn.restype, fn.argtypes = ctypes.c_int, [ctypes.c_void_p] * 3 + [ctypes.c_int32,
+                                                                     ctypes.c_void_p]
+    assert fn(da.data_ptr(), db.data_ptr(), q.data_ptr(), a.size, B._stream().value) == 0
+    got = q.cpu().numpy()
+    wrong = np.flatnonzero(got != a // b)
+    assert wrong.size == 0, (a[wrong[:5]], b[wrong[:5]], got[wrong[:5]])
