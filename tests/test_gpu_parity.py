@@ -609,11 +609,12 @@ def chunk512_inputs():
     return d, masks, parts
 
 
-@pytest.mark.parametrize("splits", [0, 3])
+@pytest.mark.parametrize("splits", [0, 3, 4])
 def test_attention_chunk512_long_context(splits, chunk512_inputs):
     """The launch the chunk-size sweep's 512-token legs run: the query tiles of a
-    512-token chunk do not fill the GPU, so num_splits = 0 picks 4 uniform
-    splits (the general merge at head_dim 128).  Estimator masks and tables vs
+    512-token chunk do not fill the GPU, so num_splits = 0 takes equal shares per
+    CU for the selected tables and 4 uniform splits for the dense ones; 3 and 4
+    are uniform splits of both (the general merge at head_dim 128).  Estimator masks and tables vs
     the oracle, every (group, query tile) sampled, the dense baseline too."""
     d, ref_masks, parts = chunk512_inputs
     w = d["workload"]
