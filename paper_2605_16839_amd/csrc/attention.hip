@@ -36,17 +36,20 @@
 //     block id, App. B.2); entries past the tile's last visible block are
 //     dropped (tables are ascending);
 //   * the workgroups of one table row run on one of the 8 XCDs and share its
-//     L2, so each page comes from HBM once; by default every row is cut in
-//     two so that the XCDs carry equal loads (xcd_cut, computed by each
-//     workgroup from the table lengths);
-//   * the XCD-balanced split's two pieces are merged inside the kernel: the
-//     second piece of a query tile to finish (an arrival counter per tile)
-//     reads the other's partial result and writes the output rows; uniform
-//     splits are merged by combine_kernel;
-//   * where query tiles and table rows would leave CUs idle (short or odd
-//     chunks, few or unequal rows), one workgroup per CU runs an equal share of
-//     all pages, a few pieces of rows (balanced_attention_kernel, the shares in
-//     kernels.hpp); combine_pieces_kernel merges them.
+//     L2, so each page comes from HBM once.
+// The launches (attn_choice in kernels.hpp picks one by the sizes):
+//   * half tiles, for short rows and chunks with much of a causal triangle:
+//     workgroups of 4 waves and 128 rows, two to a CU, no row cut;
+//   * equal shares, where query tiles and table rows would leave CUs idle (short
+//     or odd chunks, few or unequal rows): one workgroup per CU runs an equal
+//     share of all pages, a few pieces of rows (balanced_attention_kernel, the
+//     shares in kernels.hpp); combine_pieces_kernel merges them;
+//   * the XCD cut, where the tiles fill the GPU: every row in two pieces, so that
+//     the XCDs carry equal loads (xcd_cut, computed by each workgroup from the
+//     table lengths), merged inside the kernel: the second piece of a query tile
+//     to finish (an arrival counter per tile) reads the other's partial result
+//     and writes the output rows;
+//   * uniform splits of every row else; combine_kernel merges them.
 #include <atomic>
 #include <chrono>
 #include <random>
@@ -306,8 +309,7 @@ __device__ __forceinline__ void copies_landed(const T*... tiles) {
 }
 
 // NaN-propagating maximum (v_maximum3_f32 on gfx950).  fmaxf would quiet
-// each MFMA result with an extra v_max first (IEEE mode); the scores are
-// never NaN, so the two agree.
+// each MFMA result with an extra v_max first (IEEE mode), and drop a NaN.
 __device__ __forceinline__ float max3(float a, float b, float c) {
   return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
 }
@@ -1408,9 +1410,10 @@ __global__ __launch_bounds__(64 * NW, NCT == 4 ? 1 : 2) void paged_attention_ker
 //   two rows per XCD, 184 / 84 pages, D = 64 196 -> 168 us
 //   64 tokens over 16384, dense               50 -> 40 us
 //   1024 tokens over 129024, 0.3 listed      561 -> 547 us
-// A piece costs about 12 us besides its pages (walk 2.5, prologue 4.5, pages
-// outside the pipeline 3, storing 128 KB of partial results while 255 other
-// CUs do 4), which is why short rows are not cut and few pieces are made.
+// A piece costs 11 to 15 us besides its pages (walk 2.5, prologue 4.5, the drain
+// and the pages outside the pipeline 1 to 3.5, storing 128 KB of partial results
+// while 255 other CUs do 3.5 to 4.5), which is why short rows are not cut and few
+// pieces are made.
 // Merging inside the launch with arrival counters, as the XCD-balanced split
 // does, doubled the time of short launches: each counter needs a fence that
 // writes back or invalidates an XCD's whole L2, and all pieces end at once.

@@ -258,8 +258,8 @@ struct AttnSize {
   int tile_rows;            // rows of a whole tile that hold a query
   int splits;               // uniform splits
   double longest, line;     // expected entries of the longest row and of all rows
-  double full, half;        // pages per CU that whole tiles and half tiles walk
-  double unseen;            // entries that a whole tile does not see, on average
+  double full;              // pages per CU that whole tiles walk
+  double unseen, unseen_half;   // entries that a whole or half tile does not see, on average
   double xcd_share;         // pages of the XCD with the most half tiles, over the average
   bool dense;
 };
@@ -273,7 +273,7 @@ inline AttnSize attn_size(int batch, int groups, int group_size, int C, int page
   z.half_tiles = qt_half > 0 && kAttnHalfTileRows % group_size == 0 ? (C + qt_half - 1) / qt_half : 0;
   z.tile_rows = group_size * (C < qt ? C : qt);
   z.unseen = (z.tiles - 1) * (qt / (double)page) / 2;
-  const double unseen_half = (z.half_tiles - 1) * (qt_half / (double)page) / 2;
+  z.unseen_half = (z.half_tiles - 1) * (qt_half / (double)page) / 2;
   z.dense = dense;
   double load[kAttnXcds] = {};
   int max_nkb = 0;
@@ -283,14 +283,20 @@ inline AttnSize attn_size(int batch, int groups, int group_size, int C, int page
     z.longest = len > z.longest ? len : z.longest;
     z.line += groups * len;
     z.full += groups * z.tiles * (len - z.unseen) / kAttnCus;
-    z.half += groups * z.half_tiles * (len - unseen_half) / kAttnCus;
     max_nkb = nkb > max_nkb ? nkb : max_nkb;
     // half tiles of row r run on XCD r % 8 where the rows spread evenly, else the
-    // XCDs take the rows in order, an eighth each
+    // XCDs take the rows in order, an eighth of the launch each
+    const double pages = len > z.unseen_half + 1 ? len - z.unseen_half : 1;
     for (int r = b * groups; r < (b + 1) * groups; ++r) {
-      const double pages = len > unseen_half + 1 ? len - unseen_half : 1;
-      if (z.rows % kAttnXcds == 0) load[r % kAttnXcds] += pages;
-      else load[(int)((r + 0.5) * kAttnXcds / z.rows)] += pages;
+      if (z.rows % kAttnXcds == 0) {
+        load[r % kAttnXcds] += pages;
+        continue;
+      }
+      for (int x = r * kAttnXcds / z.rows; x < kAttnXcds && x * z.rows < (r + 1) * kAttnXcds; ++x) {
+        const int lo = x * z.rows > r * kAttnXcds ? x * z.rows : r * kAttnXcds;
+        const int hi = (x + 1) * z.rows < (r + 1) * kAttnXcds ? (x + 1) * z.rows : (r + 1) * kAttnXcds;
+        load[x] += pages * (hi - lo) / kAttnXcds;
+      }
     }
   }
   double most = 0, all = 0;
@@ -307,10 +313,11 @@ inline AttnSize attn_size(int batch, int groups, int group_size, int C, int page
 // Times in us of the launches where the whole tiles leave CUs idle.  The constants
 // were fitted to the choice that they make, over 2900 random sizes with every launch
 // timed (1-8 sequences, 0-130K cached, 1-3000 tokens, 4-64 heads, listed at 0.15-0.5
-// or dense, one GPU): 25 of them then take over 3% longer than with uniform splits
+// or dense, one GPU): 22 of them then take over 3% longer than with uniform splits
 // and the XCD cut alone (at most 1.25 times), 0.855 of the time in the mean.
 //   half tiles: a start, and the longest row at the rate of a workgroup that is
-//     alone on its CU, or the CU's pages at that of two;
+//     alone on its CU, or (more tiles than CUs) the longest and the shortest tile
+//     of a row side by side;
 //   equal shares: a start and the merge launch, the CU's pages, the more pieces
 //     the more tiles, and the partial results of the rows that hold a query;
 //   uniform splits: the same with pieces of the longest row, or where the pieces
@@ -322,15 +329,17 @@ struct AttnTimes {
 inline AttnTimes attn_times(const AttnSize& z, int head_dim) {
   const bool d64 = head_dim == 64;
   const double base = z.rows * (double)z.tiles / kAttnCus, held = z.tile_rows / (double)kAttnTileRows;
-  const double alone = (d64 ? 0.6 : 0.87) * z.longest, shared = 0.8 * z.half;
+  const double alone = (d64 ? 0.6 : 0.88) * z.longest;
+  const double paired = z.rows * (long long)z.half_tiles <= kAttnCus
+                            ? 0 : (d64 ? 0.9 : 1.2) * (z.longest - z.unseen_half);
   const double piece = z.longest / z.splits;
-  const double walked = base * z.splits <= 1 ? piece : z.full + 0.8 * piece;
+  const double walked = base * z.splits <= 1 ? piece : z.full + (d64 ? 1.0 : 0.7) * piece;
   AttnTimes t;
-  t.half = (d64 ? 8 : 11.5) + (alone > shared ? alone : shared);
-  t.shares = d64 ? 16.5 + 1.2 * z.full + 10 * base + 4 * held
-                 : 25 + 1.4 * z.full + 13 * base + 6 * held;
-  t.uniform = d64 ? 12 + 1.0 * walked + 8.5 * base * z.splits * held + (z.splits > 8 ? 10 : 0)
-                  : 17 + 1.4 * walked + 13 * base * z.splits * held + (z.splits > 8 ? 9 : 0);
+  t.half = (d64 ? 8 : 11.5) + (alone > paired ? alone : paired);
+  t.shares = d64 ? 16.5 + 1.1 * z.full + 10 * base + 4.5 * held
+                 : 25.5 + 1.4 * z.full + 18 * base + 5.5 * held;
+  t.uniform = d64 ? 12.5 + 1.0 * walked + 7.5 * base * z.splits * held + (z.splits > 8 ? 8 : 0)
+                  : 17.5 + 1.4 * walked + 13 * base * z.splits * held + (z.splits > 8 ? 9 : 0);
   return t;
 }
 
@@ -370,13 +379,15 @@ inline AttnChoice attn_choice(const AttnSize& z, int head_dim) {
   const AttnTimes t = attn_times(z, head_dim);
   // Equal shares, but where uniform splits give every CU one piece only if they are
   // shorter: those are as even by expectation.  Real tables differ from row to row,
-  // and from about 100 pages per CU on that outweighs what more pieces cost (rows
-  // 15% apart: equal shares 1.04-1.11 of the time at 41-95 pages, 1.0 at 130 and 210;
-  // the tables of a real selection at 157 pages: 250 us against 267 for the step).
+  // which outweighs what more pieces cost on long rows: with at most 8 rows (one per
+  // XCD) from about 64 pages per CU (rows 10% apart: 0.96-1.06 of the time at 40-51
+  // pages, 0.87-0.95 at 83), with more rows from about 100 (15% apart: 1.0-1.11 at
+  // 41-95 pages, 1.0 at 130 and 210).
   const bool one_each = tiles * z.splits == kAttnCus;
-  const bool shares = fit && (!one_each || t.shares < t.uniform || (!z.dense && z.full >= 100));
-  // 5% for the fit's error: the cut launches lose less where they are wrong
-  if (z.half_tiles > 0 && 1.05 * t.half < (shares ? t.shares : t.uniform))
+  const bool uneven = !z.dense && z.full >= (z.rows <= kAttnXcds ? 64 : 100);
+  const bool shares = fit && (!one_each || t.shares < t.uniform || uneven);
+  // 6% for the fit's error: the cut launches lose less where they are wrong
+  if (z.half_tiles > 0 && 1.06 * t.half < (shares ? t.shares : t.uniform))
     return AttnChoice::kHalfTiles;
   return shares ? AttnChoice::kShares : AttnChoice::kOther;
 }
