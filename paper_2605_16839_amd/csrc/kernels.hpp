@@ -268,45 +268,53 @@ inline AttnSize attn_size(int batch, int groups, int group_size, int C, int page
                           const int* cached_len, bool dense) {
   AttnSize z{};
   z.rows = batch * groups;
+  z.dense = dense;
   const int qt = z.query_tile = kAttnTileRows / group_size, qt_half = kAttnHalfTileRows / group_size;
   z.tiles = (C + qt - 1) / qt;
   z.half_tiles = qt_half > 0 && kAttnHalfTileRows % group_size == 0 ? (C + qt_half - 1) / qt_half : 0;
   z.tile_rows = group_size * (C < qt ? C : qt);
   z.unseen = (z.tiles - 1) * (qt / (double)page) / 2;
   z.unseen_half = (z.half_tiles - 1) * (qt_half / (double)page) / 2;
-  z.dense = dense;
-  double load[kAttnXcds] = {};
   int max_nkb = 0;
-  for (int b = 0; b < batch; ++b) {
+  auto entries = [&](int b) {
     const int nc = cached_len[b] / page, nkb = (cached_len[b] + C - 1) / page + 1;
-    const double len = dense ? nkb : nkb - nc + expected_listed(nc);
+    max_nkb = nkb > max_nkb ? nkb : max_nkb;
+    return dense ? nkb : nkb - nc + expected_listed(nc);
+  };
+  for (int b = 0; b < batch; ++b) {
+    const double len = entries(b);
     z.longest = len > z.longest ? len : z.longest;
     z.line += groups * len;
     z.full += groups * z.tiles * (len - z.unseen) / kAttnCus;
-    max_nkb = nkb > max_nkb ? nkb : max_nkb;
-    // half tiles of row r run on XCD r % 8 where the rows spread evenly, else the
-    // XCDs take the rows in order, an eighth of the launch each
-    const double pages = len > z.unseen_half + 1 ? len - z.unseen_half : 1;
-    for (int r = b * groups; r < (b + 1) * groups; ++r) {
-      if (z.rows % kAttnXcds == 0) {
-        load[r % kAttnXcds] += pages;
-        continue;
-      }
-      for (int x = r * kAttnXcds / z.rows; x < kAttnXcds && x * z.rows < (r + 1) * kAttnXcds; ++x) {
-        const int lo = x * z.rows > r * kAttnXcds ? x * z.rows : r * kAttnXcds;
-        const int hi = (x + 1) * z.rows < (r + 1) * kAttnXcds ? (x + 1) * z.rows : (r + 1) * kAttnXcds;
-        load[x] += pages * (hi - lo) / kAttnXcds;
-      }
+  }
+  z.splits = attn_uniform_splits(z.rows * z.tiles, kAttnCus, max_nkb);
+  // Half tiles of row r run on XCD r % 8 where the rows spread evenly, else the XCDs
+  // take the rows in order, an eighth of the launch each; a launch that is not a
+  // multiple of 8 workgroups is dealt out one by one.  Only the choice where whole
+  // tiles fill the GPU asks.
+  z.xcd_share = 1;
+  const long long rows = z.rows;
+  if (rows * z.tiles < kAttnCus || rows * z.half_tiles % kAttnXcds != 0 || groups % kAttnXcds == 0)
+    return z;
+  double load[kAttnXcds] = {}, most = 0, all = 0;
+  for (int b = 0; b < batch; ++b) {
+    const double len = entries(b), pages = len > z.unseen_half + 1 ? len - z.unseen_half : 1;
+    const long long r0 = (long long)b * groups, r1 = r0 + groups;
+    for (int x = 0; x < kAttnXcds; ++x) {
+      // of rows r0 .. r1-1: how many are x modulo 8, or lie in the x-th eighth
+      const long long lo = x * rows > r0 * kAttnXcds ? x * rows : r0 * kAttnXcds;
+      const long long hi = (x + 1) * rows < r1 * kAttnXcds ? (x + 1) * rows : r1 * kAttnXcds;
+      const double held = rows % kAttnXcds == 0
+                              ? (r1 + kAttnXcds - 1 - x) / kAttnXcds - (r0 + kAttnXcds - 1 - x) / kAttnXcds
+                              : hi > lo ? (hi - lo) / (double)kAttnXcds : 0;
+      load[x] += pages * held;
     }
   }
-  double most = 0, all = 0;
   for (double x : load) {
     most = x > most ? x : most;
     all += x;
   }
-  // a launch that is not a multiple of 8 workgroups is dealt out one by one
-  z.xcd_share = (long long)z.rows * z.half_tiles % kAttnXcds == 0 ? most * kAttnXcds / all : 1;
-  z.splits = attn_uniform_splits(z.rows * z.tiles, kAttnCus, max_nkb);
+  z.xcd_share = most * kAttnXcds / all;
   return z;
 }
 
