@@ -407,8 +407,15 @@ inline AttnShares attn_shares(const AttnSize& z, int C, int head_dim) {
   s.on = true;
   // one tile: its rows packed, so that a tile's rows end with the last query
   s.query_tile = n == 1 ? C : z.query_tile;
-  // a piece costs about 14 us, 8 pages of 1.6 us (D = 128); short shares lose
-  // more by rounding to it than the pieces cost
+  // A piece costs 11 to 15 us, about 8 pages of 1.6 us (D = 128), and less counts
+  // on short shares, which lose more by rounding to it than the pieces cost.  In us
+  // at costs of 4, 6, 8 and 12 pages (the one taken in brackets):
+  //     37 tokens over 65536           [40.2]  43.6   43.2   49.7
+  //    300 over 20000                   69.0  [53.4]  55.4   59.8   (taken: 5, 53.4)
+  //   1451 over 50001                  340.7  331.3  [322.5] 334.2
+  //    512 over 129024                 261.7  260.5  [260.2] 260.0
+  //   1024 over 30720 and 12345, D = 64 161.9 [160.1] 162.8  162.9
+  //     64 over 16384, dense, D = 64    [27.2]  28.8   32.4   32.3
   const int most = head_dim == 64 ? 6 : 8;
   const double o = z.line * n / kAttnCus / (head_dim == 64 ? 8 : 3);
   s.overhead = o < 4 ? 4 : o > most ? most : (int)o;
