@@ -149,16 +149,19 @@ LaunchChoice choose_launch(const ca_problem* p, const ca::Dims& d, int group_siz
                            bool dense, const void* ws, size_t ws_bytes) {
   LaunchChoice c;
   if (table_mode != ca::kTablesPerQTile) {
-    const ca::AttnSize z = ca::attn_size(d.B, d.Hq / group_size, group_size, d.C, d.page,
-                                         p->cached_len_host, dense);
-    const ca::AttnChoice choice = ca::attn_choice(z, d.D);
-    c.half = choice == ca::AttnChoice::kHalfTiles;
-    // with too little workspace (or an unaligned one) the launches below, as they take it
-    if (choice == ca::AttnChoice::kShares && ws != nullptr &&
-        reinterpret_cast<uintptr_t>(ws) % 16 == 0) {
-      const ca::AttnShares s = ca::attn_shares(z, d.C, d.D);
-      if (ws_bytes >= ca::attn_shares_ws_bytes(d, group_size, s)) c.shares = s;
+    ca::AttnSize z = ca::attn_size(d.B, d.Hq / group_size, group_size, d.C, d.page,
+                                   p->cached_len_host, dense);
+    z.splits = auto_splits(d, group_size, ws_bytes, ws != nullptr, table_mode);
+    // with too little workspace (or an unaligned one) the other launches, as they take it
+    bool fit = ca::attn_shares_fit(z) && ws != nullptr && reinterpret_cast<uintptr_t>(ws) % 16 == 0;
+    ca::AttnShares shares;
+    if (fit) {
+      shares = ca::attn_shares(z, d.C, d.D);
+      fit = ws_bytes >= ca::attn_shares_ws_bytes(d, group_size, shares);
     }
+    const ca::AttnChoice choice = ca::attn_choice(z, d.D, fit);
+    c.half = choice == ca::AttnChoice::kHalfTiles;
+    if (choice == ca::AttnChoice::kShares) c.shares = shares;
   }
   if (c.half || c.shares.on) return c;
   c.xcd = xcd_balance_ok(d, p, group_size, table_mode, dense) && ws != nullptr &&
@@ -722,7 +725,7 @@ size_t ca_attention_workspace_bytes(const ca_problem* p, int32_t group_size, int
     for (const bool dense : {false, true}) {
       const ca::AttnSize z = ca::attn_size(d.B, d.Hq / group_size, group_size, d.C, d.page,
                                            p->cached_len_host, dense);
-      if (ca::attn_choice(z, d.D) != ca::AttnChoice::kShares) continue;
+      if (ca::attn_choice(z, d.D, ca::attn_shares_fit(z)) != ca::AttnChoice::kShares) continue;
       const size_t sh = ca::attn_shares_ws_bytes(d, group_size, ca::attn_shares(z, d.C, d.D));
       need = sh > need ? sh : need;
     }

@@ -360,8 +360,9 @@ inline bool attn_shares_fit(const AttnSize& z) {
 }
 
 enum class AttnChoice { kHalfTiles, kShares, kOther };   // kOther: the XCD cut or uniform splits
-inline AttnChoice attn_choice(const AttnSize& z, int head_dim) {
-  const bool fit = attn_shares_fit(z);
+// fit: equal shares can be laid out and the workspace holds them; z.splits: the
+// uniform splits that it holds.
+inline AttnChoice attn_choice(const AttnSize& z, int head_dim, bool fit) {
   const long long tiles = (long long)z.rows * z.tiles;
   if (tiles >= kAttnCus) {
     // Whole tiles fill the GPU.  By the part of the pages that the causal triangle
@@ -383,7 +384,9 @@ inline AttnChoice attn_choice(const AttnSize& z, int head_dim) {
     return fit && !much && (rounds >= 3 || z.longest * rounds - z.full >= 24)
                ? AttnChoice::kShares : AttnChoice::kOther;
   }
-  if (z.splits == 1 && z.half_tiles > 0) return AttnChoice::kHalfTiles;   // at most 7 blocks
+  // rows of at most 7 blocks, or no workspace: no cut, and half tiles walk a page in
+  // 0.6-0.9 us where whole ones take 1.0-1.4
+  if (z.splits == 1 && z.half_tiles > 0) return AttnChoice::kHalfTiles;
   const AttnTimes t = attn_times(z, head_dim);
   // Equal shares, but where uniform splits give every CU one piece only if they are
   // shorter: those are as even by expectation.  Real tables differ from row to row,

@@ -59,7 +59,9 @@ def test_not_finite_launches(launch):
 def test_workspace_too_small(launch):
     cached, chunk, heads, dim, group, _, _ = pieces.SHARES[2]
     assert launch(cached, chunk, heads, dim, group, False, short=1) == UNIFORM + 7
-    assert launch(cached, chunk, heads, dim, group, False, ws=0) == UNIFORM + 1
+    assert launch(cached, chunk, heads, dim, group, False, ws=0) == HALF
+    # tiles that fill the GPU: whole ones
+    assert launch((129024,), 2048, (32, 8), 128, 4, False, ws=0) == UNIFORM + 1
 
 
 # Sizes at which the launch chosen by the sizes alone took longer than another (us,
