@@ -267,7 +267,8 @@ ca_status ca_estimate_tables(const ca_problem* p, const uint16_t* q, const uint1
  *    num_splits: 1 = one pass per query tile; > 1 = the table of each row is
  *    cut into that many consecutive pieces whose partial results are merged
  *    by log-sum-exp (needs workspace); 0 = let the library choose:
- *      - half tiles, for short rows and for chunks with much of a causal triangle:
+ *      - half tiles, for short rows, for chunks with much of a causal triangle,
+ *        and without a workspace where whole query tiles cannot fill the GPU:
  *        query tiles of half the size, two to a CU, no row cut (no workspace is
  *        needed);
  *      - equal shares, when fewer than 32 query tiles share at most 64 table rows,
